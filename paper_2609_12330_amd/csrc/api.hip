@@ -279,10 +279,11 @@ ef_status launch_mfma(const Shape& s, const void* q, const void* k, const void* 
   a.bm = rows_per_block(s, std::min(T, runs.lv));
   a.mtiles = (a.R + a.bm - 1) / a.bm;
   a.c_abs = std::fabs(scale) * ef::kLog2e;
+  a.qflip = scale < 0.f ? 0x80008000u : 0u;
   a.causal = causal ? 1 : 0;
   a.runs = runs;
   if (diff != nullptr) a.diff = *diff;
-  return from_hip(ef::launch_mfma_attention(a, scale < 0.f, stream));
+  return from_hip(ef::launch_mfma_attention(a, stream));
 }
 
 }  // namespace

@@ -17,25 +17,34 @@
 // is already in the B-operand layout of the second product. Two lanes
 // (l and l ^ 32) share a query and exchange one value per tile for the max.
 //
-// Software pipeline over tiles of BN keys (64, or 32 for the split producer
-// of decode shapes, whose smaller stages let four workgroups share a compute
-// unit): while the vector ALU turns tile j's
-// scores into weights, the matrix core already computes tile j+1's scores,
-// then tile j's values are multiplied. K is therefore staged one tile ahead
-// of V: during step j, K stage (j+1)%2 holds K of tile j+1 and V stage j%2
-// holds V of tile j, and the step loads K of tile j+2 and V of tile j+1 into
-// the two stages nobody reads during it, so one workgroup barrier per tile
-// suffices. Tiles go from HBM straight into LDS (direct loads, no staging
-// registers), row-major with their 16-byte chunks permuted per row so that
-// the fragment reads are free of bank conflicts. The V^T operand of the
-// second product comes from transposing LDS reads (ds_read_b64_tr_b16) of the
-// row-major V tile, in the key order of the P^T fragments.
+// Two loops share this layout and the prologue and epilogue around it:
 //
-// The maximum used as the exponent reference is only moved up when a tile's
-// maximum exceeds it by more than 8 (base-2 units), so the carried sum and
-// value are rescaled rarely; weights stay below 2^8 and the final
-// value / sum is unchanged (the repair h(c, s, s') = c * 2^(s - s') is exact
-// for any reference point).
+// The rolling loop (struct Rolling; prefill and every launch whose K/V tiles
+// are shared or whose rows fill the matrix core) works on 32-key subtiles of
+// 64-key tiles. While the vector ALU turns subtile j's scores into weights, the
+// matrix core forms subtile j + 1's scores and multiplies subtile j - 1's
+// values: three subtiles are in flight, so nothing the wave issues during a
+// subtile depends on anything else in it, and the source fixes the order of
+// issue product by product (see struct Rolling). K is staged one tile ahead of
+// V, two stages each, one workgroup barrier per 64 keys.
+//
+// The streaming loop (pipelined_step; the split producer of decode shapes)
+// works on 32-key tiles of half the LDS, four workgroups to a compute unit,
+// with non-temporal loads: it is bound by the K/V stream. Tile j's weights are
+// formed while the matrix core computes tile j + 1's scores, then tile j's
+// values are multiplied.
+//
+// Tiles go from HBM straight into LDS (direct loads, no staging registers),
+// row-major with their 16-byte chunks permuted per row so that the fragment
+// reads are free of bank conflicts. The V^T operand of the second product comes
+// from transposing LDS reads (ds_read_b64_tr_b16) of the row-major V tile, in
+// the key order of the P^T fragments.
+//
+// The exponent reference is only moved up when a weight against it may exceed
+// 2^8 (base-2 units), so the carried sum and value are rescaled rarely; the
+// final value / sum is unchanged (the repair h(c, s, s') = c * 2^(s - s') is
+// exact for any reference point). A negative scale is moved into q (bf16
+// negation is exact), so the scale c below is positive.
 //
 // In split mode the workgroup covers one key partition and stores the
 // partition's (reference, sum, value) state instead of value / sum.
@@ -52,7 +61,7 @@
 // y = A1 - lambda * A2 from the carried value, mixes in lambda from the four
 // learned vectors, RMS-normalises the row over D (the two lanes of a query
 // hold its two halves) and writes the result, so A1 never reaches HBM.
-#include <atomic>
+#include <type_traits>
 
 #include "diff_norm.hpp"
 #include "ef_device.hpp"
@@ -63,26 +72,22 @@ namespace ef {
 namespace {
 
 constexpr float kLazyThreshold = 8.f;  // base-2 headroom before the reference moves
-constexpr unsigned kXcds = 8;                   // accelerator dies of the chip
+constexpr float kLazySum = 256.f;      // 2^8: a lane's weights whose sum is below are too
+constexpr float kNoRef = -3.402823466e+38f;  // rolling loop: no key seen yet (-FLT_MAX)
+constexpr unsigned kXcds = 8;                // accelerator dies of the chip
 
-// Geometry of a BN-key tile (BN = 64, or 32 for the decode-shaped split
-// producer, whose smaller stages let four workgroups share a compute unit).
-template <int D, int BN>
+// Geometry of K and V rows in LDS.
+template <int D>
 struct TileGeom {
   static constexpr int KCH = D / 8;        // 16-byte chunks per row
   static constexpr int ROW = 2 * D;        // bytes per K or V row (no padding: swizzled)
-  static constexpr int RPI = 64 / KCH;     // rows one wave-wide direct load fills
-  static constexpr int TILE_BYTES = BN * ROW;
-  // LDS: V stage 0, V stage 1, K stage 0, K stage 1 (all immediates < 64 KiB).
-  static constexpr int V_OFF0 = 0;
-  static constexpr int V_OFF1 = TILE_BYTES;
-  static constexpr int K_OFF0 = 2 * TILE_BYTES;
-  static constexpr int K_OFF1 = 3 * TILE_BYTES;
-  static constexpr int LDS_BYTES = 4 * TILE_BYTES;
+  static constexpr int RPI = 64 / KCH;     // rows one wave-wide direct load fills (1 KiB)
+  static constexpr int SUB = 32 * ROW;     // bytes of 32 rows
+  // Streaming loop: V stage 0, V stage 1, K stage 0, K stage 1 of 32 keys each.
   template <int S>
-  static constexpr int v_off() { return S == 0 ? V_OFF0 : V_OFF1; }
+  static constexpr int v_off() { return S * SUB; }
   template <int S>
-  static constexpr int k_off() { return S == 0 ? K_OFF0 : K_OFF1; }
+  static constexpr int k_off() { return (2 + S) * SUB; }
   // Tiles sit row-major in LDS with their 16-byte chunks permuted per row
   // (chunk c of row r at slot c ^ swz(r)), so the fragment reads below hit
   // distinct banks: K rows are read 16 rows at a time at one chunk, V rows four
@@ -121,30 +126,18 @@ struct TileList {
   }
 };
 
-// Tiles go straight from HBM to LDS (one 16-byte chunk per lane and load,
-// each wave-wide load filling RPI whole rows): no staging registers and no
-// LDS stores. Rows past the tile's run repeat its last row (their keys are
-// masked, their values finite); a tile past the last one loads nothing.
-//
-// Cache policy: the split producer of decode shapes (32-key tiles, one row
-// tile per kv head) reads every key exactly once, so its loads are
-// non-temporal and stream past the caches, which lifts its read rate by
-// about a sixth; the other launches keep the default policy, under which
-// the row tiles of one kv head share its K/V tiles through the XCD's L2.
-template <bool STREAM>
-__device__ __forceinline__ void load_chunk(const uint16_t* g, char* l) {
-  if constexpr (STREAM)
-    __builtin_amdgcn_global_load_lds(g, (__attribute__((address_space(3))) void*)l, 16, 0,
-                                     2 /* non-temporal */);
-  else
-    __builtin_amdgcn_global_load_lds(g, (__attribute__((address_space(3))) void*)l, 16, 0, 0);
-}
-
-template <int D, int NW, int BN>
+// Loads of the streaming loop's 32-key tiles, straight from HBM to LDS (one
+// 16-byte chunk per lane and load, each wave-wide load filling RPI whole rows).
+// Rows past the tile's run repeat its last row (their keys are masked, their
+// values finite); a tile past the last one loads nothing. Every key is read
+// exactly once, so the loads are non-temporal and stream past the caches, which
+// lifts the read rate by about a sixth (5.5 to 6.3-6.5 TB/s on the 537 MB of a
+// 16 x 8192-key chunked decode).
+template <int D, int NW>
 struct Loader {
-  using G = TileGeom<D, BN>;
-  static constexpr int INSTS = BN / G::RPI / NW;  // direct loads per wave and tile
-  static_assert(INSTS * G::RPI * NW == BN, "tile split over the waves");
+  using G = TileGeom<D>;
+  static constexpr int INSTS = 32 / G::RPI / NW;  // direct loads per wave and tile
+  static_assert(INSTS * G::RPI * NW == 32, "tile split over the waves");
   int row[INSTS];       // tile row whose chunk this lane loads
   int kchunk[INSTS];    // element offset of that chunk in a K row
   int vchunk[INSTS];    // element offset of that chunk in a V row
@@ -167,6 +160,10 @@ struct Loader {
     }
   }
 
+  static __device__ __forceinline__ void load_chunk(const char* g, char* l) {
+    __builtin_amdgcn_global_load_lds(g, (__attribute__((address_space(3))) void*)l, 16, 0,
+                                     2 /* non-temporal */);
+  }
   // The address is a uniform base (the tile's first row) plus a 32-bit lane
   // offset, so the vector ALU only clamps rows of a ragged tile.
   template <bool ISK>
@@ -174,21 +171,16 @@ struct Loader {
     const int nrows = kend - kb;
     if (nrows <= 0) return;
     const char* base = reinterpret_cast<const char*>(head + (size_t)kb * D);
-    if (nrows >= BN) {
+    if (nrows >= 32) {
 #pragma unroll
-      for (int i = 0; i < INSTS; ++i) {
-        char* l = stage + (wave + NW * i) * 1024;
-        const uint16_t* g = reinterpret_cast<const uint16_t*>(base + (ISK ? koff[i] : voff[i]));
-        load_chunk<BN == 32>(g, l);
-      }
+      for (int i = 0; i < INSTS; ++i)
+        load_chunk(base + (ISK ? koff[i] : voff[i]), stage + (wave + NW * i) * 1024);
     } else {
 #pragma unroll
       for (int i = 0; i < INSTS; ++i) {
         const int r = min(row[i], nrows - 1);
         const unsigned off = (unsigned)(r * D + (ISK ? kchunk[i] : vchunk[i])) * 2u;
-        char* l = stage + (wave + NW * i) * 1024;
-        const uint16_t* g = reinterpret_cast<const uint16_t*>(base + off);
-        load_chunk<BN == 32>(g, l);
+        load_chunk(base + off, stage + (wave + NW * i) * 1024);
       }
     }
   }
@@ -205,101 +197,65 @@ struct Loader {
 // Waits for this wave's direct-to-LDS loads (they count as vector memory loads).
 __device__ __forceinline__ void wait_tile_loads() { __builtin_amdgcn_s_waitcnt(0x0f70); }
 
-// Occupancy target: two waves per SIMD for 4-wave workgroups (two workgroups per
-// CU overlap each other's barrier and latency stalls) and for 2-wave workgroups
-// of 32-key tiles (four per CU); the 2-wave variant with 64-key tiles keeps its
-// larger per-thread staging registers at one wave per SIMD.
-template <int NW, int BN>
-constexpr int kWavesPerEu = (NW == 4 || BN == 32) ? 2 : 1;
-
-template <int D, bool NEG, int BN>
-struct Tile {
-  using Geo = TileGeom<D, BN>;
-  static constexpr int KSTEPS = D / 16;  // MFMA k-steps over the head dimension
-  static constexpr int DT = D / 32;      // 32-wide output tiles along D
-  static constexpr int HALVES = BN / 32;  // 32-key halves of a tile
-  static constexpr int PK = BN / 4;       // packed bf16 weight pairs per lane
-
-  // S^T of the key tile in K stage S: 32-key halves, 16-deep MFMA k-steps.
-  template <int S>
-  static __device__ __forceinline__ void scores(const char* smem, const int* kread,
-                                                const bf16x8_t* qf, floatx16* sacc) {
+// Scores of the keys hidden from this lane's row set to -inf: past the run's end
+// or the causal limit `lim`, or at most `lo` (left of the window) and not a sink.
+// Element i holds key kb + 4 h + o(i) with a compile-time offset o, so the hidden
+// keys become per-lane offset thresholds, clamped to the tile so the arithmetic
+// cannot overflow: past `vis`, and inside [wlo, whi]. Selects, not branches.
+__device__ __forceinline__ void mask_scores(floatx16& x, int kb, int kend, int lim, int lo,
+                                            int sinks, int h) {
+  const int base = kb + 4 * h;
+  const int vis = min(min(kend - 1, lim), kb + 32) - base;
+  const int wlo = max(sinks, kb) - base;
+  const int whi = min(max(lo, kb - 1), kb + 32) - base;
+  if (__builtin_amdgcn_ballot_w64(whi >= wlo)) {
 #pragma unroll
-    for (int half = 0; half < HALVES; ++half)
+    for (int i = 0; i < 16; ++i) {
+      const int o = 8 * (i >> 2) + (i & 3);
+      const bool hide = (o > vis) | ((o >= wlo) & (o <= whi));
+      x[i] = hide ? kNegInf : x[i];
+    }
+  } else {
 #pragma unroll
-      for (int i = 0; i < 16; ++i) sacc[half][i] = 0.f;
-    if constexpr (HALVES == 1) {
-      // One 32-key half: each K fragment has registers of its own, so the reads
-      // can run several products ahead (the compiler issues them in two
-      // batches) rather than one product ahead.
-      u32x4_t kx[KSTEPS];
-#pragma unroll
-      for (int s = 0; s < KSTEPS; ++s)
-        kx[s] = *reinterpret_cast<const u32x4_t*>(smem + Geo::template k_off<S>() + kread[s]);
-#pragma unroll
-      for (int s = 0; s < KSTEPS; ++s)
-        sacc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, kx[s]),
-                                                         qf[s], sacc[0], 0, 0, 0);
-    } else {
-#pragma unroll
-      for (int s = 0; s < KSTEPS; ++s) {
-#pragma unroll
-        for (int half = 0; half < HALVES; ++half) {
-          const u32x4_t kx = *reinterpret_cast<const u32x4_t*>(
-              smem + Geo::template k_off<S>() + kread[s] + half * 32 * Geo::ROW);
-          sacc[half] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-              __builtin_bit_cast(bf16x8_t, kx), qf[s], sacc[half], 0, 0, 0);
-        }
-      }
+    for (int i = 0; i < 16; ++i) {
+      const int o = 8 * (i >> 2) + (i & 3);
+      x[i] = o > vis ? kNegInf : x[i];
     }
   }
+}
 
-  // Scores in exponent-ready form (sign applied, hidden keys at -inf) and the
-  // rolling reference update; returns -reference (0 while nothing is visible).
-  // A key is hidden from this lane's row when it is past the tile's run, past
-  // the causal limit `lim`, or at most `lo` (left of the window) and not a sink.
-  // The scores are rewritten in place.
-  static __device__ __forceinline__ float prepare(floatx16* x, floatx16* oacc, float& lsum,
+// S^T of the 32-key subtile at kt, every K fragment in registers of its own so
+// that the reads run several products ahead.
+template <int D>
+__device__ __forceinline__ void subtile_scores(const char* kt, const int* kread,
+                                               const bf16x8_t* qf, floatx16& sacc) {
+  u32x4_t kx[D / 16];
+#pragma unroll
+  for (int s = 0; s < D / 16; ++s) kx[s] = *reinterpret_cast<const u32x4_t*>(kt + kread[s]);
+#pragma unroll
+  for (int i = 0; i < 16; ++i) sacc[i] = 0.f;
+#pragma unroll
+  for (int s = 0; s < D / 16; ++s)
+    sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, kx[s]), qf[s],
+                                                   sacc, 0, 0, 0);
+}
+
+// Softmax and value steps of the streaming loop's 32-key tiles.
+template <int D>
+struct Tile {
+  using Geo = TileGeom<D>;
+  static constexpr int DT = D / 32;  // 32-wide output tiles along D
+
+  // Masks the scores and updates the rolling reference; returns -reference (0
+  // while nothing is visible).
+  static __device__ __forceinline__ float prepare(floatx16& x, floatx16* oacc, float& lsum,
                                                   float& mref, float c, int kb, int kend,
                                                   bool masked, int lim, int lo, int sinks,
                                                   int h) {
-    if constexpr (NEG) {
+    if (masked) mask_scores(x, kb, kend, lim, lo, sinks, h);
+    float tmax = fmaxf(x[0], x[1]);
 #pragma unroll
-      for (int half = 0; half < HALVES; ++half)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) x[half][i] = -x[half][i];
-    }
-    if (masked) {
-      // Element i of half `half` holds key base + o(i) with a compile-time offset o.
-      // The hidden keys become per-lane offset thresholds, clamped to the tile so the
-      // arithmetic cannot overflow: past `vis` (the run's end or the causal limit), and
-      // inside [wlo, whi] (left of the window, not a sink). Selects, not branches.
-      const int base = kb + 4 * h;
-      const int vis = min(min(kend - 1, lim), kb + BN) - base;
-      const int wlo = max(sinks, kb) - base;
-      const int whi = min(max(lo, kb - 1), kb + BN) - base;
-      if (__builtin_amdgcn_ballot_w64(whi >= wlo)) {
-#pragma unroll
-        for (int half = 0; half < HALVES; ++half)
-#pragma unroll
-          for (int i = 0; i < 16; ++i) {
-            const int o = half * 32 + 8 * (i >> 2) + (i & 3);
-            const bool hide = (o > vis) | ((o >= wlo) & (o <= whi));
-            x[half][i] = hide ? kNegInf : x[half][i];
-          }
-      } else {
-#pragma unroll
-        for (int half = 0; half < HALVES; ++half)
-#pragma unroll
-          for (int i = 0; i < 16; ++i) {
-            const int o = half * 32 + 8 * (i >> 2) + (i & 3);
-            x[half][i] = o > vis ? kNegInf : x[half][i];
-          }
-      }
-    }
-    float tmax = fmaxf(x[0][0], x[0][1]);
-#pragma unroll
-    for (int i = 2; i < 16 * HALVES; ++i) tmax = fmaxf(tmax, x[i >> 4][i & 15]);
+    for (int i = 2; i < 16; ++i) tmax = fmaxf(tmax, x[i]);
     tmax = max_with_other_half(tmax);
     const float cand = tmax * c;  // tile maximum in base-2 units (c > 0)
     // Move the reference only when the tile exceeds it by the threshold.
@@ -321,50 +277,23 @@ struct Tile {
   // rounded weights in half the instructions, but between matrix products it
   // costs about ten cycles each; the two sums differ by far less than the
   // rounding of the weights themselves.)
-  static __device__ __forceinline__ void weights(const floatx16* x, float c, float mneg,
+  static __device__ __forceinline__ void weights(const floatx16& x, float c, float mneg,
                                                  uint32_t* pk, float& lsum) {
     float ps[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int i = 0; i < PK; ++i) {
-      const float p0 = exp2_fast(fmaf(x[(2 * i) >> 4][(2 * i) & 15], c, mneg));
-      const float p1 = exp2_fast(fmaf(x[(2 * i + 1) >> 4][(2 * i + 1) & 15], c, mneg));
+    for (int i = 0; i < 8; ++i) {
+      const float p0 = exp2_fast(fmaf(x[2 * i], c, mneg));
+      const float p1 = exp2_fast(fmaf(x[2 * i + 1], c, mneg));
       pk[i] = pack_bf16x2(p0, p1);
       ps[i & 3] += p0 + p1;
     }
     lsum += (ps[0] + ps[1]) + (ps[2] + ps[3]);
   }
 
-  // O^T += V^T * P^T over the 16-key steps of the tile in V stage S. The
-  // V^T operand (8 keys of one value column per lane) comes from two
-  // transposing reads of 4 keys each out of the row-major V tile.
-  template <int S>
-  static __device__ __forceinline__ void values(const char* smem, const int* vread,
-                                                const uint32_t* pk, floatx16* oacc) {
-    if constexpr (BN == 32) {
-      values_asm<S>(smem, vread, pk, oacc);
-    } else {
-      typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
-#pragma unroll
-      for (int s = 0; s < BN / 16; ++s) {
-        // P^T fragment: registers 8*(s%2) .. +8 of score half s/2, i.e. pk[4*s .. 4*s+3].
-        const u32x4_t pv = {pk[4 * s], pk[4 * s + 1], pk[4 * s + 2], pk[4 * s + 3]};
-        const bf16x8_t pf = __builtin_bit_cast(bf16x8_t, pv);
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt) {
-          const char* p = smem + Geo::template v_off<S>() + vread[dt] + 16 * s * Geo::ROW;
-          const bf16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
-              (__attribute__((address_space(3))) bf16x4_t*)(p));
-          const bf16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
-              (__attribute__((address_space(3))) bf16x4_t*)(p + 8 * Geo::ROW));
-          const bf16x8_t vx = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-          oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vx, pf, oacc[dt], 0, 0, 0);
-        }
-      }
-    }
-  }
-
-  // values() of a 32-key tile with the transposing reads issued from assembly:
-  // the compiler cannot tell them from the direct-to-LDS loads into the other
+  // O^T += V^T * P^T over the two 16-key steps of the tile in V stage S; the
+  // V^T operand (8 keys of one value column per lane) comes from two transposing
+  // reads of 4 keys each out of the row-major V tile. The reads are issued from
+  // assembly: the compiler cannot tell them from the direct-to-LDS loads into the other
   // stages still in flight, and waits for every outstanding load before the
   // first of them, which leaves the step's loads only its first half to land.
   // The reads of 16-key step s + 1 are requested before the products of step
@@ -372,11 +301,11 @@ struct Tile {
   // until at most step s + 1's reads are outstanding suffices (other
   // operations counted by the same counter only make it longer). An empty
   // statement that rewrites the operands after the wait keeps the products
-  // below it. (With 64-key tiles the extra registers this holds would spill.)
+  // below it.
   template <int S>
-  static __device__ __forceinline__ void values_asm(const char* smem, const int* vread,
+  static __device__ __forceinline__ void values(const char* smem, const int* vread,
                                                     const uint32_t* pk, floatx16* oacc) {
-    constexpr int STEPS = BN / 16;
+    constexpr int STEPS = 2;
     constexpr int READS = 2 * DT;  // reads per 16-key step
     static_assert(READS <= 15, "outstanding reads exceed the LDS counter");
     const unsigned base = (unsigned)(uintptr_t)(
@@ -417,42 +346,347 @@ struct Tile {
   }
 };
 
-// One pipelined step on tile j (stage parity S = j % 2). On entry sacc[S] holds
-// S^T of tile j, K stage 1-S holds tile j+1 and V stage S holds tile j. The
-// step requests K of tile j+2 (into K stage S, last read for tile j's scores)
-// and V of tile j+1 (into V stage 1-S, last read for tile j-1's values)
+// One step of the streaming loop on tile j (stage parity S = j % 2). On entry
+// sacc[S] holds S^T of tile j, K stage 1-S holds tile j+1 and V stage S holds
+// tile j. The step requests K of tile j+2 (into K stage S, last read for tile j's
+// scores) and V of tile j+1 (into V stage 1-S, last read for tile j-1's values)
 // straight into LDS, computes tile j's weights while the matrix core computes
-// tile j+1's scores, multiplies tile j's values, and waits for its loads
-// before the workgroup barrier.
-template <int D, int NW, bool NEG, int S, int BN>
-__device__ __forceinline__ void pipelined_step(
-    char* smem, const Loader<D, NW, BN>& ld, const uint16_t* kh, const uint16_t* vh,
-    const TileList<BN>& tl, int j, int lim, int lo, int h, const int* kread, const int* vread,
-    const bf16x8_t* qf, floatx16 (*sacc)[BN / 32], floatx16* oacc, float& lsum, float& mref,
-    float c) {
-  using TileT = Tile<D, NEG, BN>;
+// tile j+1's scores, multiplies tile j's values, and waits for its loads before
+// the workgroup barrier.
+template <int D, int NW, int S>
+__device__ __forceinline__ void pipelined_step(char* smem, const Loader<D, NW>& ld,
+                                               const uint16_t* kh, const uint16_t* vh,
+                                               const TileList<32>& tl, int j, int lim, int lo,
+                                               int h, const int* kread, const int* vread,
+                                               const bf16x8_t* qf, floatx16* sacc, floatx16* oacc,
+                                               float& lsum, float& mref, float c) {
+  using TileT = Tile<D>;
   ld.template load_k<S>(smem, kh, tl.base(j + 2), tl.end(j + 2));  // nothing past the last tile
   ld.template load_v<1 - S>(smem, vh, tl.base(j + 1), tl.end(j + 1));
   const float mneg = TileT::prepare(sacc[S], oacc, lsum, mref, c, tl.base(j), tl.end(j),
                                     tl.masked(j), lim, lo, tl.sinks, h);
-  uint32_t pk[TileT::PK];
+  uint32_t pk[8];
   TileT::weights(sacc[S], c, mneg, pk, lsum);
-  // Tile j+1's scores go to the other accumulator pair, so tile j's stay in place.
-  TileT::template scores<1 - S>(smem, kread, qf, sacc[1 - S]);
+  // Tile j+1's scores go to the other accumulator, so tile j's stay in place.
+  subtile_scores<D>(smem + TileGeom<D>::template k_off<1 - S>(), kread, qf, sacc[1 - S]);
   TileT::template values<S>(smem, vread, pk, oacc);
   wait_tile_loads();
   __syncthreads();
 }
 
-template <int D, int NW, bool NEG, bool DIFF, int BN>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(kWavesPerEu<NW, BN>)))
+// Compile-time loop: f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>).
+template <int N, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (N > 0) {
+    static_for<N - 1>(f);
+    f(std::integral_constant<int, N - 1>{});
+  }
+}
+
+// The rolling loop's work on one 32-key subtile j: its softmax, beside the
+// scores of subtile j + 1 and the values of subtile j - 1.
+//
+// What bounds it: the matrix core and, on long launches, the power limit (the
+// clock falls from 2.4 to about 1.75 GHz under this loop; a library matrix
+// product of random bf16 data runs at 1.77 GHz too). Before, a step formed a
+// tile's weights and multiplied its values one after the other, took the tile's
+// maximum on every step and spent about a hundred scalar instructions on tile
+// addresses; its matrix cores were busy 54% of the time on 8192 keys at
+// D = 128, whatever order the compiler issued the step in. Here
+//  - all products of a step are independent of the softmax beside them, and
+//    scheduling barriers pin one product, its share of the vector work (3-4
+//    instructions) and the fragment reads PF products ahead to each slot;
+//  - the maximum is only taken when a lane's sum of weights passes 2^8
+//    (soft_end), 57 vector instructions per 16 weights instead of 74;
+//  - tile loads keep one address register set for all tiles (StageLoader).
+// Together 61.5% busy: 8 x 8192^2 pairs of 32 heads 1064 -> 984 us, the
+// causal 2048 prefill of 4 x 32 heads 168.5 -> 156.5 us.
+template <int D>
+struct Rolling {
+  using Geo = TileGeom<D>;
+  static constexpr int KSTEPS = D / 16;
+  static constexpr int DT = D / 32;
+  static constexpr int NV = 2 * DT;            // value products of a subtile
+  static constexpr int SLOTS = KSTEPS + NV;    // products of a subtile
+  static constexpr int PF = 6;                 // slots a fragment is read ahead of its product
+
+  // Products of a subtile in issue order: scores and values alternate, so no
+  // product follows the one it accumulates onto; the last two are values, so
+  // the scores are complete when the next subtile reads them.
+  static constexpr bool is_score(int i) {
+    return i < SLOTS - 4 ? i % 2 == 0 : i < SLOTS - 2;
+  }
+  static constexpr int index_of(int i) {  // k-step of a score slot, number of a value slot
+    int n = 0;
+    for (int k = 0; k < i; ++k) n += is_score(k) == is_score(i);
+    return n;
+  }
+
+  // Fragment offsets and operands of the wave, and the state carried along.
+  const int* kread;
+  const int* vread;
+  const bf16x8_t* qf;
+  floatx16* oacc;
+  float& lsum;
+  float& mref;
+  float c;
+
+  // Fragment of product i of a subtile, K and V subtiles at kt and vt.
+  template <int I>
+  __device__ __forceinline__ u32x4_t fragment(const char* kt, const char* vt) const {
+    constexpr int n = index_of(I);
+    if constexpr (is_score(I)) {
+      return *reinterpret_cast<const u32x4_t*>(kt + kread[n]);
+    } else {
+      typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
+      const char* p = vt + vread[n % DT] + 16 * (n / DT) * Geo::ROW;
+      const bf16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
+          (__attribute__((address_space(3))) bf16x4_t*)(p));
+      const bf16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
+          (__attribute__((address_space(3))) bf16x4_t*)(p + 8 * Geo::ROW));
+      const bf16x8_t vx = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+      return __builtin_bit_cast(u32x4_t, vx);
+    }
+  }
+
+  template <int I>
+  __device__ __forceinline__ void product(const u32x4_t& fr, floatx16& y, const uint32_t* pin) {
+    constexpr int n = index_of(I);
+    if constexpr (is_score(I)) {
+      if constexpr (n == 0) {
+        floatx16 z;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) z[i] = 0.f;
+        y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, fr), qf[0], z, 0,
+                                                   0, 0);
+      } else {
+        y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, fr), qf[n], y, 0,
+                                                   0, 0);
+      }
+    } else {
+      constexpr int s = n / DT, dt = n % DT;
+      const u32x4_t pv = {pin[4 * s], pin[4 * s + 1], pin[4 * s + 2], pin[4 * s + 3]};
+      oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+          __builtin_bit_cast(bf16x8_t, fr), __builtin_bit_cast(bf16x8_t, pv), oacc[dt], 0, 0, 0);
+    }
+  }
+
+  // One subtile's softmax (scores x, weights pout) beside the other subtiles'
+  // products: slot I's share of the weights 2^(x c - reference) and their sum.
+  struct Soft {
+    float ps[4];
+    float prev;
+  };
+  template <int I, int N>
+  __device__ __forceinline__ void soft_slot(Soft& f, const floatx16& x, uint32_t* pout) const {
+    constexpr int lo = 16 * I / N, hi = 16 * (I + 1) / N;
+    static_for<hi - lo>([&](auto q) {
+      constexpr int e = lo + decltype(q)::value;
+      const float p = exp2_fast(fmaf(x[e], c, -mref));
+      if constexpr (e % 2 == 0) {
+        f.prev = p;
+      } else {
+        pout[e / 2] = pack_bf16x2(f.prev, p);
+        if constexpr (e / 2 < 4)
+          f.ps[e / 2] = f.prev + p;
+        else
+          f.ps[e / 2 - 4] += f.prev + p;
+        // Keeps the weights' work in this slot (the compiler would sink it past
+        // the branch of soft_end, next to its use).
+        asm volatile("" : "+v"(pout[e / 2]), "+v"(f.ps[(e / 2) % 4]));
+      }
+    });
+  }
+  // A lane's weights are all at most 2^8 when their sum is, and then the
+  // reference stays. Otherwise (the first visible keys of a row, or a larger
+  // score) the reference moves up to the subtile's maximum, the carried sum and
+  // value are rescaled and the weights formed again.
+  __device__ __forceinline__ void soft_end(Soft& f, const floatx16& x, uint32_t* pout,
+                                           bool values) {
+    float sum = (f.ps[0] + f.ps[1]) + (f.ps[2] + f.ps[3]);
+    if (__builtin_amdgcn_ballot_w64(!(sum <= kLazySum))) {
+      float tmax = fmaxf(x[0], x[1]);
+#pragma unroll
+      for (int i = 2; i < 16; ++i) tmax = fmaxf(tmax, x[i]);
+      const float cand = max_with_other_half(tmax) * c;
+      const float old = mref;
+      mref = fmaxf(mref, cand);
+      const float rs = exp2_fast(old - mref);  // 1 where the reference stayed
+      lsum *= rs;
+      if (values) {
+#pragma unroll
+        for (int i = 0; i < DT; ++i)
+#pragma unroll
+          for (int jj = 0; jj < 16; ++jj) oacc[i][jj] *= rs;
+      }
+      soft_slot<0, 1>(f, x, pout);
+      sum = (f.ps[0] + f.ps[1]) + (f.ps[2] + f.ps[3]);
+    }
+    lsum += sum;
+  }
+
+  // Subtile softmax of x into pout, the next subtile's scores into y (K subtile
+  // at kt) and, with VALUES, the values of the previous subtile (V subtile at
+  // vt, weights pin). fr: fragments; with CARRY_IN the first PF are already in
+  // fr[0..PF), with CARRY_OUT the next subtile's first PF are left there.
+  template <bool VALUES, bool CARRY_IN, bool CARRY_OUT>
+  __device__ __forceinline__ void subtile(const floatx16& x, floatx16& y, const uint32_t* pin,
+                                          uint32_t* pout, const char* kt, const char* vt,
+                                          const char* kt2, const char* vt2, u32x4_t* carry) {
+    u32x4_t fr[SLOTS];
+    static_for<PF>([&](auto i) {
+      constexpr int I = decltype(i)::value;
+      if constexpr (VALUES || is_score(I)) {
+        if constexpr (CARRY_IN) fr[I] = carry[I];
+        else fr[I] = fragment<I>(kt, vt);
+      }
+    });
+    __builtin_amdgcn_sched_barrier(0);
+    Soft f;
+    static_for<SLOTS>([&](auto i) {
+      constexpr int I = decltype(i)::value;
+      if constexpr (I + PF < SLOTS) {
+        if constexpr (VALUES || is_score(I + PF)) fr[I + PF] = fragment<I + PF>(kt, vt);
+      } else if constexpr (CARRY_OUT) {
+        carry[I + PF - SLOTS] = fragment<I + PF - SLOTS>(kt2, vt2);
+      }
+      if constexpr (VALUES || is_score(I)) product<I>(fr[I], y, pin);
+      soft_slot<I, SLOTS>(f, x, pout);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    soft_end(f, x, pout, VALUES);
+  }
+
+  // Values of the last subtile.
+  __device__ __forceinline__ void last_values(const uint32_t* pin, const char* vt) {
+    static_for<SLOTS>([&](auto i) {
+      constexpr int I = decltype(i)::value;
+      if constexpr (!is_score(I)) {
+        floatx16 unused;
+        product<I>(fragment<I>(nullptr, vt), unused, pin);
+      }
+    });
+  }
+};
+
+// One 64-key tile of the list: its first key, the end of its run, and whether
+// some key of it is hidden from some row of the workgroup.
+struct TileAt {
+  int base, end;
+  bool masked;
+};
+__device__ __forceinline__ TileAt tile_at(const TileList<64>& tl, int t) {
+  return {tl.base(t), tl.end(t), tl.masked(t)};
+}
+
+// Loads of 64-key tiles into the stages of the rolling loop. Wave w loads the
+// rows [64 w / NW, 64 (w + 1) / NW) of a tile, one 1 KiB block of whole rows per
+// instruction; block i lies i KiB further both in memory and in LDS, so the
+// instruction offset serves both and only the lane offsets of K, whose chunk
+// permutation has a period of 16 rows, differ from block to block.
+template <int D, int NW>
+struct StageLoader {
+  using G = TileGeom<D>;
+  static constexpr int INSTS = 64 / G::RPI / NW;
+  static constexpr int KPER = D == 128 ? 4 : 2;  // blocks of the K permutation's period
+  static constexpr int NK = INSTS < KPER ? INSTS : KPER;
+  __amdgpu_buffer_rsrc_t krs, vrs;
+  unsigned koff[NK], voff;
+  int row0, slot;  // this lane's row in the wave's block 0, and its 16-byte slot
+  int wbase;       // byte offset of the wave's first block in a tile (scalar)
+
+  __device__ __forceinline__ void init(const uint16_t* kh, const uint16_t* vh) {
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    krs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(kh), (short)0, -1, 0x00020000);
+    vrs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(vh), (short)0, -1, 0x00020000);
+    wbase = wave * INSTS * 1024;
+    row0 = wave * INSTS * G::RPI + lane / G::KCH;
+    slot = lane % G::KCH;
+#pragma unroll
+    for (int i = 0; i < NK; ++i)
+      koff[i] = row0 * G::ROW + (slot ^ G::swz_k(row0 + i * G::RPI)) * 16;
+    voff = row0 * G::ROW + (slot ^ G::swz_v(row0)) * 16;
+  }
+  // Block I of a whole tile.
+  template <bool ISK, int I>
+  __device__ __forceinline__ void block(char* l, unsigned soff) const {
+    constexpr int hi = I / 4 * 4096;  // past the 12-bit instruction offset
+    if constexpr (ISK)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(
+          krs, (__attribute__((address_space(3))) void*)(l + hi), 16, (int)koff[I % NK],
+          (int)(soff + hi), I % 4 * 1024, 0);
+    else
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(
+          vrs, (__attribute__((address_space(3))) void*)(l + hi), 16, (int)voff,
+          (int)(soff + hi), I % 4 * 1024, 0);
+  }
+  template <bool ISK>
+  __device__ __forceinline__ void load(char* stage, int kb, int kend) const {
+    const int nrows = kend - kb;
+    if (nrows <= 0) return;  // a tile past the last one
+    char* l = stage + wbase;
+    const unsigned soff = (unsigned)kb * G::ROW;
+    if (nrows >= 64) {
+      static_for<INSTS>([&](auto q) { block<ISK, decltype(q)::value>(l, soff); });
+    } else {
+      // Ragged tile: rows past the run repeat its last row (masked later).
+#pragma unroll
+      for (int i = 0; i < INSTS; ++i) {
+        const int r = row0 + i * G::RPI;
+        const int c = slot ^ (ISK ? G::swz_k(r) : G::swz_v(r));
+        const int off = min(r, nrows - 1) * G::ROW + c * 16;
+        auto* d = (__attribute__((address_space(3))) void*)(l + i * 1024);
+        if constexpr (ISK)
+          __builtin_amdgcn_raw_ptr_buffer_load_lds(krs, d, 16, off, (int)soff, 0, 0);
+        else
+          __builtin_amdgcn_raw_ptr_buffer_load_lds(vrs, d, 16, off, (int)soff, 0, 0);
+      }
+    }
+  }
+};
+
+// One step of the rolling loop, tiles t0 = u, t1 = u + 1, t2 = u + 2: the softmax
+// of the second half of tile u (scores in xa) and of the first half of tile u + 1
+// (xb, if `second`), beside the scores of tile u + 1 (K stage `knext`) and the
+// values of tile u (V stage `vcur`, weights of its first half in pb on entry).
+// Meanwhile K of tile u + 2 and V of tile u + 1 land in the two stages nobody
+// reads during the step.
+template <int D, int NW>
+__device__ __forceinline__ void pair_step(char* knext, char* kfree, char* vcur, char* vfree,
+                                          Rolling<D>& ro, const StageLoader<D, NW>& ld,
+                                          const TileAt& t0, const TileAt& t1, const TileAt& t2,
+                                          bool second, int lim, int lo, int sinks, int h,
+                                          floatx16& xa, floatx16& xb, uint32_t* pa, uint32_t* pb) {
+  using R = Rolling<D>;
+  constexpr int SUB = TileGeom<D>::SUB;
+  u32x4_t carry[R::PF];
+  ld.template load<true>(kfree, t2.base, t2.end);
+  ld.template load<false>(vfree, t1.base, t1.end);
+  if (t0.masked) mask_scores(xa, t0.base + 32, t0.end, lim, lo, sinks, h);
+  ro.template subtile<true, false, true>(xa, xb, pb, pa, knext, vcur, knext + SUB,
+                                         vcur + SUB, carry);
+  if (second) {
+    if (t1.masked) mask_scores(xb, t1.base, t1.end, lim, lo, sinks, h);
+    ro.template subtile<true, true, false>(xb, xa, pa, pb, knext + SUB, vcur + SUB, nullptr,
+                                           nullptr, carry);
+  }
+  wait_tile_loads();
+  __syncthreads();
+}
+
+// Occupancy target: two waves per SIMD (two workgroups of four waves per CU, four
+// of the streaming loop's two-wave ones, overlap each other's barrier and
+// latency stalls); the two-wave workgroup of the rolling loop serves grids too
+// small for a second wave per SIMD.
+template <int D, int NW, bool STREAM, bool DIFF>
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 4 || STREAM ? 2 : 1)))
 void attn_mfma_kernel(MfmaParams a) {
-  using Geo = TileGeom<D, BN>;
-  using TileT = Tile<D, NEG, BN>;
-  constexpr int KSTEPS = TileT::KSTEPS;
-  constexpr int DT = TileT::DT;
+  using Geo = TileGeom<D>;
+  constexpr int KSTEPS = D / 16;
+  constexpr int DT = D / 32;
   constexpr int BM = 32 * NW;
-  extern __shared__ __align__(16) char smem[];
+  constexpr int BN = STREAM ? 32 : 64;  // keys per tile
 
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
@@ -526,7 +760,7 @@ void attn_mfma_kernel(MfmaParams a) {
     const u32x4_t zero = {0u, 0u, 0u, 0u};
 #pragma unroll
     for (int s = 0; s < KSTEPS; ++s) {
-      u32x4_t x = rvalid ? qp[2 * s + h] : zero;
+      const u32x4_t x = (rvalid ? qp[2 * s + h] : zero) ^ a.qflip;
       qf[s] = __builtin_bit_cast(bf16x8_t, x);
     }
   }
@@ -536,7 +770,7 @@ void attn_mfma_kernel(MfmaParams a) {
   for (int i = 0; i < DT; ++i)
 #pragma unroll
     for (int j = 0; j < 16; ++j) oacc[i][j] = 0.f;
-  float mref = kNegInf;  // reference maximum, base-2 units
+  float mref = STREAM ? kNegInf : kNoRef;  // reference maximum, base-2 units
   float lsum = 0.f;      // this lane's half of the row sum
   // The floor keeps a zero scale well defined: every visible key gets weight 1
   // (2^(x c) rounds to 1 for any finite score), while a hidden key's -inf stays
@@ -560,29 +794,77 @@ void attn_mfma_kernel(MfmaParams a) {
     }
   }
 
-  // Prologue: K and V of tile 0 into stage 0, K of tile 1 into K stage 1, then
-  // tile 0's scores; the second barrier orders those K reads before stage 0 is
-  // rewritten by the first pipelined step.
-  Loader<D, NW, BN> ld;
-  ld.init();
-  floatx16 sacc[2][BN / 32];  // S^T of the current and the next tile
-  if (ntiles > 0) {
-    ld.template load_k<0>(smem, kh, tl.base(0), tl.end(0));
-    ld.template load_v<0>(smem, vh, tl.base(0), tl.end(0));
-    ld.template load_k<1>(smem, kh, tl.base(1), tl.end(1));
+  if constexpr (STREAM) {
+    // Prologue: K and V of tile 0 into stage 0, K of tile 1 into K stage 1, then
+    // tile 0's scores; the second barrier orders those K reads before stage 0 is
+    // rewritten by the first step.
+    __shared__ __align__(1024) char smem[4 * Geo::SUB];
+    Loader<D, NW> ld;
+    ld.init();
+    floatx16 sacc[2];  // S^T of the current and the next tile
+    if (ntiles > 0) {
+      ld.template load_k<0>(smem, kh, tl.base(0), tl.end(0));
+      ld.template load_v<0>(smem, vh, tl.base(0), tl.end(0));
+      ld.template load_k<1>(smem, kh, tl.base(1), tl.end(1));
+    }
+    wait_tile_loads();
+    __syncthreads();
+    if (ntiles > 0) subtile_scores<D>(smem + Geo::template k_off<0>(), kread, qf, sacc[0]);
+    __syncthreads();
+    for (int j = 0; j < ntiles; j += 2) {
+      pipelined_step<D, NW, 0>(smem, ld, kh, vh, tl, j, lim, lo, h, kread, vread, qf, sacc, oacc,
+                               lsum, mref, c);
+      if (j + 1 < ntiles)
+        pipelined_step<D, NW, 1>(smem, ld, kh, vh, tl, j + 1, lim, lo, h, kread, vread, qf, sacc,
+                                 oacc, lsum, mref, c);
+    }
+  } else if (ntiles > 0) {
+    // The four stages are objects of their own, and the loads go through buffer
+    // descriptors: the compiler then neither waits for a step's loads before its
+    // first reads (they cannot alias) nor drains the LDS counter at every read
+    // (it does with a flat direct-to-LDS load in flight).
+    __shared__ __align__(1024) char k0[2 * Geo::SUB], k1[2 * Geo::SUB];
+    __shared__ __align__(1024) char v0[2 * Geo::SUB], v1[2 * Geo::SUB];
+    floatx16 xa, xb;        // scores of odd and even subtiles
+    uint32_t pa[8], pb[8];  // their weights
+    Rolling<D> ro{kread, vread, qf, oacc, lsum, mref, c};
+    StageLoader<D, NW> ld;
+    ld.init(kh, vh);
+    TileAt t0 = tile_at(tl, 0), t1 = tile_at(tl, 1), t2;
+    // Subtiles; the last tile's second half may lie past its run.
+    const int nsub = 2 * ntiles - (tl.base(ntiles - 1) + 32 >= tl.end(ntiles - 1) ? 1 : 0);
+    // Prologue: tile 0's K and V and tile 1's K; subtile 0's scores, then its
+    // softmax beside subtile 1's scores. The second barrier orders those K reads
+    // before stage 0 is rewritten by the first step.
+    ld.template load<true>(k0, t0.base, t0.end);
+    ld.template load<false>(v0, t0.base, t0.end);
+    ld.template load<true>(k1, t1.base, t1.end);
+    wait_tile_loads();
+    __syncthreads();
+    subtile_scores<D>(k0, kread, qf, xb);
+    if (t0.masked) mask_scores(xb, t0.base, t0.end, lim, lo, tl.sinks, h);
+    ro.template subtile<false, false, false>(xb, xa, nullptr, pb, k0 + Geo::SUB, nullptr, nullptr,
+                                             nullptr, nullptr);
+    __syncthreads();
+    for (int u = 0; 2 * u + 1 < nsub; u += 2) {
+      t2 = tile_at(tl, u + 2);
+      pair_step<D, NW>(k1, k0, v0, v1, ro, ld, t0, t1, t2, 2 * u + 2 < nsub, lim, lo, tl.sinks, h,
+                       xa, xb, pa, pb);
+      if (2 * u + 3 >= nsub) break;
+      t0 = tile_at(tl, u + 3);
+      pair_step<D, NW>(k0, k1, v1, v0, ro, ld, t1, t2, t0, 2 * u + 4 < nsub, lim, lo, tl.sinks, h,
+                       xa, xb, pa, pb);
+      t1 = t0;
+      t0 = t2;
+    }
+    const int last = nsub - 1;
+    const char* vl = (last >> 1 & 1) ? v1 : v0;
+    if (last & 1)
+      ro.last_values(pa, vl + Geo::SUB);
+    else
+      ro.last_values(pb, vl);
   }
-  wait_tile_loads();
-  __syncthreads();
-  if (ntiles > 0) TileT::template scores<0>(smem, kread, qf, sacc[0]);
-  __syncthreads();
-
-  for (int j = 0; j < ntiles; j += 2) {
-    pipelined_step<D, NW, NEG, 0, BN>(smem, ld, kh, vh, tl, j, lim, lo, h, kread, vread, qf,
-                                      sacc, oacc, lsum, mref, c);
-    if (j + 1 < ntiles)
-      pipelined_step<D, NW, NEG, 1, BN>(smem, ld, kh, vh, tl, j + 1, lim, lo, h, kread, vread,
-                                        qf, sacc, oacc, lsum, mref, c);
-  }
+  if (mref == kNoRef) mref = kNegInf;
 
   // Row sum over both lane halves.
   const float ltot = lsum + __shfl_xor(lsum, 32, 64);
@@ -657,54 +939,31 @@ void attn_mfma_kernel(MfmaParams a) {
   }
 }
 
-template <int D, int NW, bool NEG, bool DIFF, int BN>
+template <int D, int NW, bool STREAM, bool DIFF>
 hipError_t launch_one(const MfmaParams& a, hipStream_t stream) {
-  const size_t lds = TileGeom<D, BN>::LDS_BYTES;
-  auto kern = attn_mfma_kernel<D, NW, NEG, DIFF, BN>;
-  // More than 64 KiB of LDS per workgroup needs the attribute, which belongs to
-  // the kernel on one device: set once per device (ids below 64 are
-  // remembered, higher ones set it on every launch).
-  static std::atomic<unsigned long long> lds_set{0};
-  int dev = 0;
-  const hipError_t de = hipGetDevice(&dev);
-  if (de != hipSuccess) return de;
-  const unsigned long long bit = (dev >= 0 && dev < 64) ? 1ull << dev : 0ull;
-  if (bit == 0 || (lds_set.load(std::memory_order_acquire) & bit) == 0) {
-    const hipError_t attr = hipFuncSetAttribute(
-        reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (attr != hipSuccess) return attr;
-    lds_set.fetch_or(bit, std::memory_order_acq_rel);
-  }
-  dim3 grid(a.mtiles, a.P, a.B * a.Hkv);
-  hipLaunchKernelGGL(kern, grid, dim3(NW * 64), lds, stream, a);
+  hipLaunchKernelGGL((attn_mfma_kernel<D, NW, STREAM, DIFF>), dim3(a.mtiles, a.P, a.B * a.Hkv),
+                     dim3(NW * 64), 0, stream, a);
   return hipGetLastError();
 }
 
-template <int D, int NW, int BN>
-hipError_t launch_nw(const MfmaParams& a, bool neg, hipStream_t stream) {
-  if (a.diff.gamma != nullptr)
-    return neg ? launch_one<D, NW, true, true, BN>(a, stream)
-               : launch_one<D, NW, false, true, BN>(a, stream);
-  return neg ? launch_one<D, NW, true, false, BN>(a, stream)
-             : launch_one<D, NW, false, false, BN>(a, stream);
+template <int D>
+hipError_t launch_d(const MfmaParams& a, hipStream_t stream) {
+  const bool diff = a.diff.gamma != nullptr;
+  // The split producer with one 64-row tile per kv head (decode shapes) streams:
+  // its loads assume that every key is read once.
+  if (a.bm == 64 && a.mtiles == 1 && a.ws_m != nullptr) return launch_one<D, 2, true, false>(a, stream);
+  if (a.bm == 64)
+    return diff ? launch_one<D, 2, false, true>(a, stream)
+                : launch_one<D, 2, false, false>(a, stream);
+  return diff ? launch_one<D, 4, false, true>(a, stream)
+              : launch_one<D, 4, false, false>(a, stream);
 }
 
 }  // namespace
 
-hipError_t launch_mfma_attention(const MfmaParams& a, bool neg, hipStream_t stream) {
-  const int bm = a.bm;
-  if (bm != 64 && bm != 128) return hipErrorInvalidValue;
-  // The split producer with one row tile per kv head (decode shapes) runs
-  // 32-key tiles, whose non-temporal loads assume every key is read once.
-  const bool small = bm == 64 && a.mtiles == 1 && a.ws_m != nullptr;
-  if (a.D == 128) {
-    if (small) return launch_nw<128, 2, 32>(a, neg, stream);
-    if (bm == 64) return launch_nw<128, 2, 64>(a, neg, stream);
-    return launch_nw<128, 4, 64>(a, neg, stream);
-  }
-  if (small) return launch_nw<64, 2, 32>(a, neg, stream);
-  if (bm == 64) return launch_nw<64, 2, 64>(a, neg, stream);
-  return launch_nw<64, 4, 64>(a, neg, stream);
+hipError_t launch_mfma_attention(const MfmaParams& a, hipStream_t stream) {
+  if (a.bm != 64 && a.bm != 128) return hipErrorInvalidValue;
+  return a.D == 128 ? launch_d<128>(a, stream) : launch_d<64>(a, stream);
 }
 
 }  // namespace ef

@@ -82,6 +82,7 @@ struct MfmaParams {
   int bm;        // query rows per workgroup: 64 (two waves) or 128 (four)
   int mtiles;    // query-row tiles per kv head
   float c_abs;   // |scale| * log2(e)
+  uint32_t qflip;  // 0x80008000 for a negative scale (q is negated), else 0
   int causal;
   KeyRuns runs;  // split mode: partitions cover the virtual key axis
   // Differential attention, single pass only: with diff.gamma set this launch
@@ -104,7 +105,7 @@ struct CombineParams {
 // Fill of an fp32 buffer with zeros (output rows that see no key).
 hipError_t launch_zero_fill(float* p, size_t n, hipStream_t stream);
 hipError_t launch_decode_split(const DecodeParams& a, hipStream_t stream);
-hipError_t launch_mfma_attention(const MfmaParams& a, bool negative_scale, hipStream_t stream);
+hipError_t launch_mfma_attention(const MfmaParams& a, hipStream_t stream);
 hipError_t launch_combine(const CombineParams& a, hipStream_t stream);
 
 
