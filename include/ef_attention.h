@@ -259,7 +259,8 @@ double ef_attention_splitkv_modeled_us(int B, int Hq, int Hkv, int Sq, int Skv, 
  * peak; the smallest wins, and with equal times the one with less matrix
  * work. `keys`: the keys a row tile streams (Skv for a full or causal
  * prefill, the partition size in a split-KV call). Returns 0 for invalid
- * sizes or keys < 0.
+ * sizes or keys < 0. (A single-pass launch too small to fill the chip runs
+ * 64-row tiles whose keys two groups of waves share, whatever this returns.)
  */
 int ef_attention_rows_per_workgroup(int B, int Hq, int Hkv, int Sq, int Skv, int D, int keys);
 
@@ -293,17 +294,19 @@ ef_status ef_attention_splitkv_tune(const void* q, const void* k, const void* v,
  *   y = A1 - lambda * A2
  *   o = (1 - lambda_init) * norm_weight * y / sqrt(mean(y^2) + eps),
  * and o = 0 for a row where mean(y^2) + eps is 0 (y = 0 with eps = 0). The
- * weight, the difference and the normalisation are applied by one kernel as
- * the first branch's output is formed, so no A1 tensor is written.
+ * weight, the difference and the normalisation are applied as the branches'
+ * outputs are formed, so no A1 tensor is written.
  *   q1, q2 : [B][Hq][Sq][D] bf16; k1, k2, v : [B][Hkv][Skv][D] bf16;
- *   o      : [B][Hq][Sq][D] fp32, also used to hold A2 between the branches.
+ *   o      : [B][Hq][Sq][D] fp32, also used to hold A2 between the branches of
+ *            a split call.
  *   lambda_q1, lambda_k1, lambda_q2, lambda_k2, norm_weight : [D] fp32 device
  *            buffers, shared by all heads; norm_weight 16-byte aligned.
  *   lambda_init, eps : finite, eps >= 0 (else EF_ERR_INVALID_DIFF).
- *   partition_size : 0 (model choice, as for ef_attention_splitkv) or a
+ *   partition_size : 0 (the library's choice: one partition when the query rows
+ *            alone fill the chip, else as for ef_attention_splitkv) or a
  *            positive multiple of 64. When the resolved partition covers every
- *            key each branch is one single-pass launch and the workspace is not
- *            used (it may be NULL); otherwise each branch runs the split-KV
+ *            key both branches run in one single-pass launch and the workspace
+ *            is not used (it may be NULL); otherwise each branch runs the split-KV
  *            producer into `workspace` (ef_diff_attention_workspace_size bytes,
  *            16-byte aligned, reused by both branches) and its combine.
  * Other errors as for ef_attention_splitkv; all buffers are caller-owned and

@@ -36,6 +36,9 @@ HIP_FLAGS = [
     "-fPIC",
     "-Wall",
     "-Wno-unused-function",
+    # matrix-core accumulators in VGPRs (a kernel over 256 registers otherwise moves its
+    # score tile from AGPRs to VGPRs on every 32 keys: 16 instructions)
+    "-mllvm", "-amdgpu-mfma-vgpr-form=1",
     # packed fp32 (v_pk_*_f32) selection off
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     f"-I{INCLUDE}",

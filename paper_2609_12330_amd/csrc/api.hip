@@ -259,9 +259,30 @@ bool fused_combine(const Shape& s, long long P, int d_splits) {
 
 ef_status from_hip(hipError_t e) { return e == hipSuccess ? EF_OK : EF_ERR_HIP; }
 
+// Whether a single-pass launch runs 64-row tiles whose key tiles two groups of
+// waves share (MfmaParams::key_split). A launch with fewer workgroups than the
+// chip holds waits for its longest chain of key tiles, which two groups halve;
+// with more, the rows of a 128-row workgroup make better use of each staged
+// tile. The two-group workgroup takes 128 KiB of LDS at D = 128 (one per CU) and
+// 64 KiB at D = 64 (two), so the line is one round of them; causal launches, whose
+// later workgroups are short, go a quarter past it. Measured, one group of 64 or
+// 128 rows against two groups (us; 64-row tiles in brackets): D = 128 full,
+// 4096^2 x 4 heads [256] 66.9 / 47.6; causal 1024 of 8192
+// keys x 16 heads [256] 127.0 / 87.0, 32/8 heads 640 [320] 17.7 / 16.8, 777 [392]
+// 20.4 / 20.8, 16/4 heads 2048 [512] 39.5 / 41.8; 64 rows of 4000 keys x 32 [32]
+// 63.2 / 45.7; D = 64, 4 x 16 heads 384 full [384] 10.2 / 9.8, 16 heads 2048
+// causal [512] 29.7 / 23.6, 8 x 12 heads 384 full [576] 13.5 / 15.9.
+bool use_key_split(const Shape& s, int keys, int causal) {
+  const long long R = (long long)(s.Hq / s.Hkv) * s.Sq;
+  const long long tiles = (long long)s.B * s.Hkv * ((R + 63) / 64);
+  const long long slots = s.D == 128 ? 256 : 512;
+  return keys > kTileKeys && tiles <= (causal ? slots + slots / 4 : slots);
+}
+
 ef_status launch_mfma(const Shape& s, const void* q, const void* k, const void* v, float* o,
                       float* ws_m, float* ws_l, float* ws_acc, int T, int P, float scale,
                       int causal, const ef::KeyRuns& runs, hipStream_t stream,
+                      const void* q2 = nullptr, const void* k2 = nullptr,
                       const ef::DiffParams* diff = nullptr) {
   ef::MfmaParams a{};
   a.q = static_cast<const uint16_t*>(q);
@@ -282,7 +303,15 @@ ef_status launch_mfma(const Shape& s, const void* q, const void* k, const void* 
   a.qflip = scale < 0.f ? 0x80008000u : 0u;
   a.causal = causal ? 1 : 0;
   a.runs = runs;
-  if (diff != nullptr) a.diff = *diff;
+  if (diff != nullptr) {
+    a.q2 = static_cast<const uint16_t*>(q2);
+    a.k2 = static_cast<const uint16_t*>(k2);
+    a.diff = *diff;
+  } else if (ws_m == nullptr && use_key_split(s, runs.lv, causal)) {
+    a.key_split = 1;
+    a.bm = 64;
+    a.mtiles = (a.R + 63) / 64;
+  }
   return from_hip(ef::launch_mfma_attention(a, stream));
 }
 
@@ -666,12 +695,25 @@ ef_status ef_attention_splitkv_tune(const void* q, const void* k, const void* v,
 
 namespace {
 
+// Row tiles of 128 rows from which a differential layer left to the library
+// runs as one launch over both branches (a workgroup of eight waves per tile and
+// CU) whatever the model would split: from about three quarters of the chip's
+// CUs on, the second producer, the two combines and the stored states cost more
+// than the idle CUs. Measured, split / one launch (us): 12 heads of 64, 4 x 512
+// of 2048 keys [192 tiles] 63.6 / 43.6; 32/8 heads of 128, 1024 of 8192 [256]
+// 282 / 244; 32 heads, 1024 of 32768 [256] 1003 / 996; but 512 of 16384 [128]
+// 290 / 411.
+constexpr long long kDiffPairTiles = 192;
+
 // Number of partitions ef_diff_attention uses (1 = single pass), or 0 for an
 // invalid shape or partition size.
 long long diff_partitions(const Shape& s, int partition_size, int* T_out) {
   if (check_shape(s) != EF_OK) return 0;
   if (partition_size < 0 || partition_size % kTileKeys != 0) return 0;
   if (s.rows() == 0 || s.Skv == 0) return 1;
+  const long long R = (long long)(s.Hq / s.Hkv) * s.Sq;
+  if (partition_size == 0 && R > 64 && (long long)s.B * s.Hkv * ((R + 127) / 128) >= kDiffPairTiles)
+    return 1;
   const int T = resolve_partition(s, s.Skv, partition_size, s.Skv);
   *T_out = T;
   return (s.Skv + (long long)T - 1) / T;
@@ -736,11 +778,8 @@ ef_status ef_diff_attention(const void* q1, const void* q2, const void* k1, cons
                             eps};
   const ef::KeyRuns runs = key_runs(Sq, Skv, 0, 0);
   if (P == 1) {
-    st = launch_mfma(s, q2, k2, v, o, nullptr, nullptr, nullptr, runs.lv, 1, scale, causal, runs,
-                     hs);
-    if (st != EF_OK) return st;
     return launch_mfma(s, q1, k1, v, o, nullptr, nullptr, nullptr, runs.lv, 1, scale, causal,
-                       runs, hs, &diff);
+                       runs, hs, q2, k2, &diff);
   }
   const WsLayout w = ws_layout(s.rows(), P, s.D);
   if (workspace == nullptr || workspace_bytes < w.bytes) return EF_ERR_WORKSPACE_TOO_SMALL;

@@ -56,13 +56,10 @@
 // causal end. Both runs feed the same rolling reducer, so the sink and window
 // keys share one softmax normalisation; the keys in between are never read.
 //
-// Differential attention (section 7.3), single pass: the launch for the first
-// branch finds the second branch's output in o, and its epilogue forms
-// y = A1 - lambda * A2 from the carried value, mixes in lambda from the four
-// learned vectors, RMS-normalises the row over D (the two lanes of a query
-// hold its two halves) and writes the result, so A1 never reaches HBM.
-#include <type_traits>
-
+// Differential attention (section 7.3), single pass: one launch, two groups of
+// waves, one per branch. They meet in LDS, form y = A1 - lambda * A2, mix in
+// lambda from the four learned vectors, RMS-normalise the row over D and write
+// the result, so neither branch's output reaches HBM.
 #include "diff_norm.hpp"
 #include "ef_device.hpp"
 #include "ef_kernels.hpp"
@@ -575,12 +572,24 @@ struct TileAt {
   int base, end;
   bool masked;
 };
-__device__ __forceinline__ TileAt tile_at(const TileList<64>& tl, int t) {
-  return {tl.base(t), tl.end(t), tl.masked(t)};
-}
 
-// Loads of 64-key tiles into the stages of the rolling loop. Wave w loads the
-// rows [64 w / NW, 64 (w + 1) / NW) of a tile, one 1 KiB block of whole rows per
+// The tiles [first, first + n) of the list that one group of waves walks.
+struct GroupTiles {
+  const TileList<64>& tl;
+  int first, n;
+  __device__ __forceinline__ TileAt at(int t) const {
+    if (t >= n) return {0, 0, false};  // nothing to load
+    return {tl.base(first + t), tl.end(first + t), tl.masked(first + t)};
+  }
+  // 32-key subtiles; the list's last tile may end within its first half.
+  __device__ __forceinline__ int subtiles() const {
+    if (n <= 0) return 0;
+    return 2 * n - (tl.base(first + n - 1) + 32 >= tl.end(first + n - 1) ? 1 : 0);
+  }
+};
+
+// Loads of 64-key tiles into the stages of the rolling loop. Wave w of the NW
+// that share the stages loads the rows [64 w / NW, 64 (w + 1) / NW) of a tile, one 1 KiB block of whole rows per
 // instruction; block i lies i KiB further both in memory and in LDS, so the
 // instruction offset serves both and only the lane offsets of K, whose chunk
 // permutation has a period of 16 rows, differ from block to block.
@@ -595,9 +604,8 @@ struct StageLoader {
   int row0, slot;  // this lane's row in the wave's block 0, and its 16-byte slot
   int wbase;       // byte offset of the wave's first block in a tile (scalar)
 
-  __device__ __forceinline__ void init(const uint16_t* kh, const uint16_t* vh) {
+  __device__ __forceinline__ void init(const uint16_t* kh, const uint16_t* vh, int wave) {
     const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     krs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(kh), (short)0, -1, 0x00020000);
     vrs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(vh), (short)0, -1, 0x00020000);
     wbase = wave * INSTS * 1024;
@@ -671,25 +679,53 @@ __device__ __forceinline__ void pair_step(char* knext, char* kfree, char* vcur, 
     ro.template subtile<true, true, false>(xb, xa, pa, pb, knext + SUB, vcur + SUB, nullptr,
                                            nullptr, carry);
   }
-  wait_tile_loads();
-  __syncthreads();
 }
 
+// Forms of the kernel.
+enum Form {
+  kStream,    // streaming loop (split producer of decode shapes)
+  kRolling,   // rolling loop
+  kKeySplit,  // rolling loop, two groups of waves over the two halves of the key tiles
+  kDiffPair,  // rolling loop, two groups of waves over the two branches of a
+              // differential layer
+};
+
+// NW waves (of 32 query rows each) per group; the two-group forms hold two
+// groups over the same rows, with stages of their own, that meet in LDS at the
+// end.
+//
+// kKeySplit serves grids that leave the chip's SIMDs without a second wave: one
+// wave alone reaches 88% of the rate of two on a SIMD, so what such a launch
+// waits for is the chain of a workgroup's tiles, and two groups halve it. 8 heads
+// of 64, 2048 causal: 28.3 -> 17.7 us; 32/8 heads of 128, 4 x 100 of 1500 keys:
+// 30.2 -> 22.5 us (the rule that selects it holds both sides' figures).
+//
+// kDiffPair runs both branches of a differential layer in one launch: the
+// second branch's output stays in registers and LDS instead of going through o
+// between two launches. 32/8 heads of 128, 1024 causal: 52.5 -> 37.8 us, 4 x 1024:
+// 118.5 -> 108 us, 8 x 2048: 658 -> 647 us.
+//
 // Occupancy target: two waves per SIMD (two workgroups of four waves per CU, four
 // of the streaming loop's two-wave ones, overlap each other's barrier and
-// latency stalls); the two-wave workgroup of the rolling loop serves grids too
-// small for a second wave per SIMD.
-template <int D, int NW, bool STREAM, bool DIFF>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 4 || STREAM ? 2 : 1)))
+// latency stalls; a workgroup of eight waves has both on its own); the
+// four-wave two-group form and the two-wave workgroup of the rolling loop serve
+// grids too small for that.
+template <int D, int NW, Form F>
+__global__ __launch_bounds__(NW * 64 * (F >= kKeySplit ? 2 : 1))
+__attribute__((amdgpu_waves_per_eu(NW == 2 && F != kStream ? 1 : D == 64 ? 3 : 2)))
 void attn_mfma_kernel(MfmaParams a) {
   using Geo = TileGeom<D>;
+  constexpr bool STREAM = F == kStream;
+  constexpr int GROUPS = F >= kKeySplit ? 2 : 1;
   constexpr int KSTEPS = D / 16;
   constexpr int DT = D / 32;
   constexpr int BM = 32 * NW;
   constexpr int BN = STREAM ? 32 : 64;  // keys per tile
 
   const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
+  const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int grp = GROUPS > 1 ? wid / NW : 0;  // group of this wave
+  const int wave = wid - grp * NW;            // wave inside the group
   const int h = lane >> 5;   // k-group of the MFMA operands
   const int ql = lane & 31;  // this lane's query inside the wave's 32 rows
 
@@ -707,7 +743,7 @@ void attn_mfma_kernel(MfmaParams a) {
   const int b = bh / a.Hkv, hkv = bh % a.Hkv;
 
   const size_t kvhead = ((size_t)b * a.Hkv + hkv) * (size_t)a.Skv * D;
-  const uint16_t* kh = a.k + kvhead;
+  const uint16_t* kh = (F == kDiffPair && grp ? a.k2 : a.k) + kvhead;
   const uint16_t* vh = a.v + kvhead;
 
   // This lane's query row.
@@ -756,7 +792,7 @@ void attn_mfma_kernel(MfmaParams a) {
   // Q^T fragments (B operand): lane holds q[row][16*s + 8*h .. +8].
   bf16x8_t qf[KSTEPS];
   {
-    const u32x4_t* qp = reinterpret_cast<const u32x4_t*>(a.q + orow * D);
+    const u32x4_t* qp = reinterpret_cast<const u32x4_t*>((F == kDiffPair && grp ? a.q2 : a.q) + orow * D);
     const u32x4_t zero = {0u, 0u, 0u, 0u};
 #pragma unroll
     for (int s = 0; s < KSTEPS; ++s) {
@@ -818,145 +854,213 @@ void attn_mfma_kernel(MfmaParams a) {
         pipelined_step<D, NW, 1>(smem, ld, kh, vh, tl, j + 1, lim, lo, h, kread, vread, qf, sacc,
                                  oacc, lsum, mref, c);
     }
-  } else if (ntiles > 0) {
+    if (mref == kNoRef) mref = kNegInf;
+  }
+
+  // Output rows: value / sum, or the state of the partition, of the value tiles
+  // [DT0, DT0 + NDT) (32 channels each; lane halves hold alternate 4-channel runs).
+  auto store = [&](const floatx16* val, int dt0, auto ndt, float ref, float ltot, bool state) {
+    constexpr int NDT = decltype(ndt)::value;
+    if (!rvalid) return;
+    auto put = [&](float* dst, float mul) {
+#pragma unroll
+      for (int i = 0; i < NDT; ++i)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4)
+          *reinterpret_cast<float4*>(dst + (dt0 + i) * 32 + 8 * q4 + 4 * h) =
+              make_float4(val[i][4 * q4] * mul, val[i][4 * q4 + 1] * mul, val[i][4 * q4 + 2] * mul,
+                          val[i][4 * q4 + 3] * mul);
+    };
+    if (a.ws_m == nullptr) {
+      put(a.o + orow * D, ltot > 0.f ? 1.f / ltot : 0.f);
+    } else {
+      const size_t slot = orow * (size_t)a.P + p;
+      if (state && h == 0) {
+        // Reference in natural-log units, in terms of scale * q.k.
+        a.ws_m[slot] = ref == kNegInf || ref == kNoRef ? kNegInf : ref * kLn2;
+        a.ws_l[slot] = ltot;
+      }
+      put(a.ws_acc + slot * D, 1.f);
+    }
+  };
+
+  if constexpr (STREAM) {
+    store(oacc, 0, std::integral_constant<int, DT>{}, mref, lsum + __shfl_xor(lsum, 32, 64), true);
+    return;
+  } else {
     // The four stages are objects of their own, and the loads go through buffer
     // descriptors: the compiler then neither waits for a step's loads before its
     // first reads (they cannot alias) nor drains the LDS counter at every read
     // (it does with a flat direct-to-LDS load in flight).
-    __shared__ __align__(1024) char k0[2 * Geo::SUB], k1[2 * Geo::SUB];
-    __shared__ __align__(1024) char v0[2 * Geo::SUB], v1[2 * Geo::SUB];
+    constexpr int STAGE = 2 * Geo::SUB;  // one group's bytes of a stage
+    __shared__ __align__(1024) char sk0[GROUPS * STAGE], sk1[GROUPS * STAGE];
+    __shared__ __align__(1024) char sv0[GROUPS * STAGE], sv1[GROUPS * STAGE];
+    char* const k0 = sk0 + grp * STAGE;
+    char* const k1 = sk1 + grp * STAGE;
+    char* const v0 = sv0 + grp * STAGE;
+    char* const v1 = sv1 + grp * STAGE;
+    // Tiles of this group, and the steps the workgroup's barriers count: those of
+    // the first half of the tiles, which is never the shorter one.
+    const int first_half = (ntiles + 1) / 2;
+    const GroupTiles gt{tl, F == kKeySplit && grp ? first_half : 0,
+                        F != kKeySplit ? ntiles : grp ? ntiles - first_half : first_half};
+    const int nsub = gt.subtiles();
+    const int steps =
+        F == kKeySplit ? GroupTiles{tl, 0, first_half}.subtiles() / 2 : nsub / 2;
     floatx16 xa, xb;        // scores of odd and even subtiles
     uint32_t pa[8], pb[8];  // their weights
     Rolling<D> ro{kread, vread, qf, oacc, lsum, mref, c};
-    StageLoader<D, NW> ld;
-    ld.init(kh, vh);
-    TileAt t0 = tile_at(tl, 0), t1 = tile_at(tl, 1), t2;
-    // Subtiles; the last tile's second half may lie past its run.
-    const int nsub = 2 * ntiles - (tl.base(ntiles - 1) + 32 >= tl.end(ntiles - 1) ? 1 : 0);
-    // Prologue: tile 0's K and V and tile 1's K; subtile 0's scores, then its
-    // softmax beside subtile 1's scores. The second barrier orders those K reads
-    // before stage 0 is rewritten by the first step.
-    ld.template load<true>(k0, t0.base, t0.end);
-    ld.template load<false>(v0, t0.base, t0.end);
-    ld.template load<true>(k1, t1.base, t1.end);
-    wait_tile_loads();
-    __syncthreads();
-    subtile_scores<D>(k0, kread, qf, xb);
-    if (t0.masked) mask_scores(xb, t0.base, t0.end, lim, lo, tl.sinks, h);
-    ro.template subtile<false, false, false>(xb, xa, nullptr, pb, k0 + Geo::SUB, nullptr, nullptr,
-                                             nullptr, nullptr);
-    __syncthreads();
-    for (int u = 0; 2 * u + 1 < nsub; u += 2) {
-      t2 = tile_at(tl, u + 2);
-      pair_step<D, NW>(k1, k0, v0, v1, ro, ld, t0, t1, t2, 2 * u + 2 < nsub, lim, lo, tl.sinks, h,
-                       xa, xb, pa, pb);
-      if (2 * u + 3 >= nsub) break;
-      t0 = tile_at(tl, u + 3);
-      pair_step<D, NW>(k0, k1, v1, v0, ro, ld, t1, t2, t0, 2 * u + 4 < nsub, lim, lo, tl.sinks, h,
-                       xa, xb, pa, pb);
-      t1 = t0;
-      t0 = t2;
+    if (ntiles > 0) {
+      StageLoader<D, NW> ld;
+      ld.init(kh, vh, wave);
+      TileAt t0 = gt.at(0), t1 = gt.at(1), t2;
+      // Prologue: tile 0's K and V and tile 1's K; subtile 0's scores, then its
+      // softmax beside subtile 1's scores. The second barrier orders those K reads
+      // before stage 0 is rewritten by the first step.
+      ld.template load<true>(k0, t0.base, t0.end);
+      ld.template load<false>(v0, t0.base, t0.end);
+      ld.template load<true>(k1, t1.base, t1.end);
+      wait_tile_loads();
+      __syncthreads();
+      if (GROUPS == 1 || nsub > 0) {
+        subtile_scores<D>(k0, kread, qf, xb);
+        if (t0.masked) mask_scores(xb, t0.base, t0.end, lim, lo, tl.sinks, h);
+        ro.template subtile<false, false, false>(xb, xa, nullptr, pb, k0 + Geo::SUB, nullptr,
+                                                 nullptr, nullptr, nullptr);
+      }
+      __syncthreads();
+      for (int u = 0; u < steps; u += 2) {
+        t2 = gt.at(u + 2);
+        if (GROUPS == 1 || 2 * u + 1 < nsub)
+          pair_step<D, NW>(k1, k0, v0, v1, ro, ld, t0, t1, t2, 2 * u + 2 < nsub, lim, lo, tl.sinks,
+                           h, xa, xb, pa, pb);
+        wait_tile_loads();
+        __syncthreads();
+        if (u + 1 >= steps) break;
+        t0 = gt.at(u + 3);
+        if (GROUPS == 1 || 2 * u + 3 < nsub)
+          pair_step<D, NW>(k0, k1, v1, v0, ro, ld, t1, t2, t0, 2 * u + 4 < nsub, lim, lo, tl.sinks,
+                           h, xa, xb, pa, pb);
+        wait_tile_loads();
+        __syncthreads();
+        t1 = t0;
+        t0 = t2;
+      }
+      if (GROUPS == 1 || nsub > 0) {
+        const int last = nsub - 1;
+        const char* vl = (last >> 1 & 1) ? v1 : v0;
+        if (last & 1)
+          ro.last_values(pa, vl + Geo::SUB);
+        else
+          ro.last_values(pb, vl);
+      }
     }
-    const int last = nsub - 1;
-    const char* vl = (last >> 1 & 1) ? v1 : v0;
-    if (last & 1)
-      ro.last_values(pa, vl + Geo::SUB);
-    else
-      ro.last_values(pb, vl);
-  }
-  if (mref == kNoRef) mref = kNegInf;
-
-  // Row sum over both lane halves.
-  const float ltot = lsum + __shfl_xor(lsum, 32, 64);
-  if constexpr (DIFF) {
-    // Differential attention, first branch (section 7.3): mix with the second
-    // branch's output already in o and normalise the row. Lanes l and l ^ 32
-    // hold the two halves of a row.
-    const float lam = diff_lambda(a.diff, lane, D);
-    const float inv = ltot > 0.f ? 1.f / ltot : 0.f;
-    const float* prev = a.o + orow * D;
-    float ss = 0.f;
+    const float ltot = lsum + __shfl_xor(lsum, 32, 64);  // both lane halves of the row
+    if constexpr (GROUPS == 1) {
+      store(oacc, 0, std::integral_constant<int, DT>{}, mref, ltot, true);
+    } else {
+      // The groups meet: each sends the other half of its value tiles (and its
+      // reference and sum), and finishes its own half of the channels.
+      constexpr int HT = DT / 2;
+      const float inv = ltot > 0.f ? 1.f / ltot : 0.f;
+      float4* out = reinterpret_cast<float4*>(grp ? sk1 : sk0) + wave * (HT * 4 * 64) + lane;
+      const float4* in = reinterpret_cast<const float4*>(grp ? sk0 : sk1) + wave * (HT * 4 * 64) + lane;
+      float2* ml = reinterpret_cast<float2*>(sv0);  // [group][wave][lane]
+      float* sq2 = reinterpret_cast<float*>(sv1);   // [group][wave][lane]
+      floatx16 own[HT];
+      __syncthreads();
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
+      for (int i = 0; i < HT; ++i) {
 #pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        const int d = dt * 32 + 8 * q4 + 4 * h;
-        const float4 a2 = rvalid ? *reinterpret_cast<const float4*>(prev + d)
-                                 : make_float4(0.f, 0.f, 0.f, 0.f);
-        const float a2v[4] = {a2.x, a2.y, a2.z, a2.w};
+        for (int e = 0; e < 16; ++e) own[i][e] = grp ? oacc[HT + i][e] : oacc[i][e];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float y = fmaf(-lam, a2v[e], oacc[dt][4 * q4 + e] * inv);
-          oacc[dt][4 * q4 + e] = y;
-          ss = fmaf(y, y, ss);
+        for (int q4 = 0; q4 < 4; ++q4) {
+          float x[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            x[e] = grp ? oacc[i][4 * q4 + e] : oacc[HT + i][4 * q4 + e];
+            if constexpr (F == kDiffPair) x[e] *= inv;
+          }
+          out[(i * 4 + q4) * 64] = make_float4(x[0], x[1], x[2], x[3]);
         }
       }
-    const float rn = diff_row_factor(a.diff, ss + __shfl_xor(ss, 32, 64), D);
-    if (!rvalid) return;
-    float* orp = a.o + orow * D;
+      ml[(grp * NW + wave) * 64 + lane] = make_float2(mref, ltot);
+      __syncthreads();
+      if constexpr (F == kKeySplit) {
+        const float2 other = ml[((1 - grp) * NW + wave) * 64 + lane];
+        const float ref = fmaxf(mref, other.x);
+        const float wo = exp2_fast(mref - ref), wi = exp2_fast(other.x - ref);
+        const float lt = fmaf(other.y, wi, ltot * wo);
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
+        for (int i = 0; i < HT; ++i)
 #pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        const int d = dt * 32 + 8 * q4 + 4 * h;
-        const float4 gw = *reinterpret_cast<const float4*>(a.diff.gamma + d);
-        *reinterpret_cast<float4*>(orp + d) =
-            make_float4(rn * gw.x * oacc[dt][4 * q4], rn * gw.y * oacc[dt][4 * q4 + 1],
-                        rn * gw.z * oacc[dt][4 * q4 + 2], rn * gw.w * oacc[dt][4 * q4 + 3]);
+          for (int q4 = 0; q4 < 4; ++q4) {
+            const float4 x = in[(i * 4 + q4) * 64];
+            own[i][4 * q4] = fmaf(x.x, wi, own[i][4 * q4] * wo);
+            own[i][4 * q4 + 1] = fmaf(x.y, wi, own[i][4 * q4 + 1] * wo);
+            own[i][4 * q4 + 2] = fmaf(x.z, wi, own[i][4 * q4 + 2] * wo);
+            own[i][4 * q4 + 3] = fmaf(x.w, wi, own[i][4 * q4 + 3] * wo);
+          }
+        store(own, grp * HT, std::integral_constant<int, HT>{}, ref, lt, grp == 0);
+      } else {
+        // y = A1 - lambda A2 (the first group holds the first branch), then the
+        // RMS normalisation of the row over all channels.
+        const float lam = diff_lambda(a.diff, lane, D);
+        float ss = 0.f;
+#pragma unroll
+        for (int i = 0; i < HT; ++i)
+#pragma unroll
+          for (int q4 = 0; q4 < 4; ++q4) {
+            const float4 x4 = in[(i * 4 + q4) * 64];
+            const float x[4] = {x4.x, x4.y, x4.z, x4.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const float mine = own[i][4 * q4 + e] * inv;
+              const float y = fmaf(-lam, grp ? mine : x[e], grp ? x[e] : mine);
+              own[i][4 * q4 + e] = y;
+              ss = fmaf(y, y, ss);
+            }
+          }
+        ss += __shfl_xor(ss, 32, 64);
+        sq2[(grp * NW + wave) * 64 + lane] = ss;
+        __syncthreads();
+        ss += sq2[((1 - grp) * NW + wave) * 64 + lane];
+        const float rn = diff_row_factor(a.diff, ss, D);
+        if (!rvalid) return;
+        float* orp = a.o + orow * D;
+#pragma unroll
+        for (int i = 0; i < HT; ++i)
+#pragma unroll
+          for (int q4 = 0; q4 < 4; ++q4) {
+            const int d = (grp * HT + i) * 32 + 8 * q4 + 4 * h;
+            const float4 gw = *reinterpret_cast<const float4*>(a.diff.gamma + d);
+            *reinterpret_cast<float4*>(orp + d) =
+                make_float4(rn * gw.x * own[i][4 * q4], rn * gw.y * own[i][4 * q4 + 1],
+                            rn * gw.z * own[i][4 * q4 + 2], rn * gw.w * own[i][4 * q4 + 3]);
+          }
       }
-    return;
-  }
-  if (!rvalid) return;
-  if (a.ws_m == nullptr) {
-    const float inv = ltot > 0.f ? 1.f / ltot : 0.f;
-    float* orp = a.o + orow * D;
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        const int d = dt * 32 + 8 * q4 + 4 * h;
-        float4 val = make_float4(oacc[dt][4 * q4] * inv, oacc[dt][4 * q4 + 1] * inv,
-                                 oacc[dt][4 * q4 + 2] * inv, oacc[dt][4 * q4 + 3] * inv);
-        *reinterpret_cast<float4*>(orp + d) = val;
-      }
-  } else {
-    const size_t slot = orow * (size_t)a.P + p;
-    if (h == 0) {
-      // Reference in natural-log units, in terms of scale * q.k (sign restored).
-      a.ws_m[slot] = (mref == kNegInf) ? kNegInf : mref * kLn2;
-      a.ws_l[slot] = ltot;
     }
-    float* ap = a.ws_acc + slot * D;
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        const int d = dt * 32 + 8 * q4 + 4 * h;
-        *reinterpret_cast<float4*>(ap + d) =
-            make_float4(oacc[dt][4 * q4], oacc[dt][4 * q4 + 1], oacc[dt][4 * q4 + 2],
-                        oacc[dt][4 * q4 + 3]);
-      }
   }
 }
 
-template <int D, int NW, bool STREAM, bool DIFF>
+template <int D, int NW, Form F>
 hipError_t launch_one(const MfmaParams& a, hipStream_t stream) {
-  hipLaunchKernelGGL((attn_mfma_kernel<D, NW, STREAM, DIFF>), dim3(a.mtiles, a.P, a.B * a.Hkv),
-                     dim3(NW * 64), 0, stream, a);
+  hipLaunchKernelGGL((attn_mfma_kernel<D, NW, F>), dim3(a.mtiles, a.P, a.B * a.Hkv),
+                     dim3(NW * 64 * (F >= kKeySplit ? 2 : 1)), 0, stream, a);
   return hipGetLastError();
 }
 
 template <int D>
 hipError_t launch_d(const MfmaParams& a, hipStream_t stream) {
-  const bool diff = a.diff.gamma != nullptr;
+  if (a.diff.gamma != nullptr)
+    return a.bm == 64 ? launch_one<D, 2, kDiffPair>(a, stream)
+                      : launch_one<D, 4, kDiffPair>(a, stream);
+  if (a.key_split) return launch_one<D, 2, kKeySplit>(a, stream);
+  if (a.bm == 128) return launch_one<D, 4, kRolling>(a, stream);
   // The split producer with one 64-row tile per kv head (decode shapes) streams:
   // its loads assume that every key is read once.
-  if (a.bm == 64 && a.mtiles == 1 && a.ws_m != nullptr) return launch_one<D, 2, true, false>(a, stream);
-  if (a.bm == 64)
-    return diff ? launch_one<D, 2, false, true>(a, stream)
-                : launch_one<D, 2, false, false>(a, stream);
-  return diff ? launch_one<D, 4, false, true>(a, stream)
-              : launch_one<D, 4, false, false>(a, stream);
+  if (a.mtiles == 1 && a.ws_m != nullptr) return launch_one<D, 2, kStream>(a, stream);
+  return launch_one<D, 2, kRolling>(a, stream);
 }
 
 }  // namespace

@@ -85,8 +85,11 @@ struct MfmaParams {
   uint32_t qflip;  // 0x80008000 for a negative scale (q is negated), else 0
   int causal;
   KeyRuns runs;  // split mode: partitions cover the virtual key axis
+  int key_split;  // 64-row tiles, two groups of waves over the halves of the key tiles
   // Differential attention, single pass only: with diff.gamma set this launch
-  // is the first branch and o already holds the second branch's output.
+  // forms both branches (q, k and q2, k2 over one v) and their mix.
+  const uint16_t* q2;
+  const uint16_t* k2;
   DiffParams diff;
 };
 

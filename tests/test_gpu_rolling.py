@@ -1,5 +1,7 @@
 """GPU parity of the matrix-core kernel's rolling loop at the edges of its 32-key subtiles,
-64-key tiles and two-tile steps, and on scores that move its exponent reference.
+64-key tiles and two-tile steps, and on scores that move its exponent reference; of its
+key-split form (small grids) and plain form (many heads), and of the two-branch launch of a
+differential layer.
 
 Tolerance: every weight is rounded to bf16 (relative 2^-9) for the value product while the
 row sum adds the fp32 weights, so |o - ref| <= 2^-9 sum_j p_j |v_j| / l plus fp32 rounding,
@@ -31,12 +33,16 @@ def _check(q, k, v, scale, causal, what, window=0, sinks=0):
     assert err.max() <= 1e-2, f"{what}: max {err.max():.3e}"
 
 
+KEY_COUNTS = (1, 2, 31, 32, 33, 63, 64, 65, 95, 96, 97, 127, 128, 129, 160, 161, 191, 192, 193,
+              224, 225, 256, 257, 320, 321, 385)
+
+
 @pytest.mark.parametrize("D", [64, 128])
-@pytest.mark.parametrize("rows", [40, 130])  # two-wave and four-wave workgroups
+@pytest.mark.parametrize("rows", [40, 130])
 def test_key_counts(D, rows):
-    """Every remainder class of the key count: within a subtile, a tile, a two-tile step."""
-    for n in (1, 2, 31, 32, 33, 63, 64, 65, 95, 96, 97, 127, 128, 129, 160, 161, 191, 192, 193,
-              224, 225, 256, 257, 320, 321):
+    """Every remainder class of the key count: within a subtile, a tile, a two-tile step (one
+    kv head: more than one key tile runs the key-split form)."""
+    for n in KEY_COUNTS:
         q, k, v = wl.make_shape_inputs(1, 2, 1, rows // 2, n, D, seed=n)
         for causal in (False, True):
             _check(q, k, v, 1.0 / math.sqrt(D), causal, f"keys {n} rows {rows} D{D} {causal}")
@@ -68,3 +74,58 @@ def test_reference_moves(D, sign, order):
     k = (k.float() + sign * 4.0 * math.sqrt(D) * ramp * u).to(torch.bfloat16)
     for causal in (False, True):
         _check(q, k, v, sign / math.sqrt(D), causal, f"{order} {sign} D{D} {causal}")
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("rows", [40, 130])  # two-wave and four-wave workgroups
+@pytest.mark.parametrize("window,sinks", [(0, 0), (70, 5)])
+def test_key_counts_many_heads(D, rows, window, sinks):
+    """The plain form: more 64-row tiles than a round of key-split workgroups; three heads are
+    compared."""
+    H = 700
+    for n in KEY_COUNTS[::3] if window else KEY_COUNTS:
+        q, k, v = wl.make_shape_inputs(1, H, H, rows, n, D, seed=n)
+        what = f"{H} heads keys {n} rows {rows} D{D} W{window}"
+        announce(what)
+        scale = 1.0 / math.sqrt(D)
+        o = ef.attention_fwd(q.cuda(), k.cuda(), v.cuda(), scale=scale, causal=True,
+                             window=window, sinks=sinks)
+        torch.cuda.synchronize()
+        for h in (0, 311, H - 1):
+            one = slice(h, h + 1)
+            ref = oracle.attention_ref(f64(q[:, one]), f64(k[:, one]), f64(v[:, one]), scale, True,
+                                       window=window, sinks=sinks)
+            err = np.abs(o[:, one].cpu().double().numpy() - ref)
+            assert err.max() <= 1e-2, f"{what} head {h}: max {err.max():.3e}"
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("rows", [24, 130])
+def test_diff_pair_key_counts(D, rows):
+    """Both branches in one launch (one partition). y = A1 - lambda A2 is normalised to unit
+    RMS, so the bound of the branches' outputs, 2^-9 max|v| (1 + |lambda|), is divided by the
+    row's RMS of y and scaled by (1 - lambda_init) |gamma|."""
+    for n in KEY_COUNTS[2::4]:
+        q1, q2, k1, k2, v, lam, gamma = wl.make_diff_inputs(1, 2, 1, rows, n, D, seed=n)
+        what = f"diff keys {n} rows {rows} D{D}"
+        announce(what)
+        dev = [t.cuda() for t in (q1, q2, k1, k2, v)]
+        vecs = [t.cuda() for t in lam + (gamma,)]
+        o = ef.diff_attention(*dev, *vecs, wl.DIFF_LAMBDA_INIT, wl.DIFF_EPS, causal=False,
+                              partition_size=64 * (n // 64 + 1))
+        torch.cuda.synchronize()
+        scale = 1.0 / math.sqrt(D)
+        a1 = oracle.attention_ref(f64(q1), f64(k1), f64(v), scale, False)
+        a2 = oracle.attention_ref(f64(q2), f64(k2), f64(v), scale, False)
+        l64 = [t.double().numpy() for t in lam]
+        mix = np.exp(l64[0] @ l64[1]) - np.exp(l64[2] @ l64[3]) + wl.DIFF_LAMBDA_INIT
+        y = a1 - mix * a2
+        rms = np.sqrt((y * y).mean(-1, keepdims=True) + wl.DIFF_EPS)
+        g = gamma.double().numpy()
+        ref = (1.0 - wl.DIFF_LAMBDA_INIT) * g * y / rms
+        # Each branch is off by at most 2^-9 sum_j p_j |v_j| / l <= 2^-9 max|v|; the row's RMS
+        # moves by no more than the same amount.
+        dy = 2.0 ** -9 * float(v.float().abs().max()) * (1.0 + abs(mix))
+        bound = (1.0 - wl.DIFF_LAMBDA_INIT) * np.abs(g) * (dy / rms) * (1.0 + np.abs(y) / rms)
+        err = np.abs(o.cpu().double().numpy() - ref)
+        assert (err <= bound + 1e-6).all(), f"{what}: {(err / (bound + 1e-6)).max():.3f} of bound"
