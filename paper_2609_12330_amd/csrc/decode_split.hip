@@ -465,9 +465,21 @@ constexpr int kWaves = (RMAX == 1 || RMAX == 4) ? 1 : 2;
 template <int RMAX>
 constexpr int kSlots = RMAX <= 2 ? 4 : 2;
 
-template <int D, int RMAX, bool LOCAL, int DS>
-static hipError_t launch_decode_rl(const DecodeParams& a, hipStream_t stream) {
-  constexpr int NW = kWaves<RMAX>;
+// With 3 or 4 rows per kv head and few workgroups (two per CU or fewer), four
+// waves share each partition: one wave per partition leaves most SIMDs empty,
+// has too few loads in flight and, as the last arrival, combines the group's
+// rows with 64 threads. The line is where four waves stop winning on every
+// shape tried, one wave / four waves (us), 32/8 heads of 128: 2 x 8192 keys in
+// 256s [512 workgroups] 22.8 / 19.9, 4 x 4096 in 256s [512] 24.0 / 18.9, 1 x
+// 4096 [256] 15.1 / 11.1, 16/4 heads 65536 in 1024s [256] 66.5 / 30.4; heads of
+// 64, 2 x 8192 in 256s [512] 15.3 / 14.7; but 4 x 6144 in 256s [768] 24.6 / 30.7
+// and 8 x 4096 [1024] 27.9 / 33.6. (1 or 2 rows: within 10% either way.) It
+// counts partitions only, so every channel split of a problem has the same
+// waves and the same sums.
+constexpr long long kWideWorkgroups = 512;
+
+template <int D, int RMAX, int NW, bool LOCAL, int DS>
+static hipError_t launch_decode_nw(const DecodeParams& a, hipStream_t stream) {
   constexpr int U = kSlots<RMAX>;
   dim3 grid(a.P * DS, a.Hkv, a.B);
   if (a.counters != nullptr) {
@@ -478,6 +490,15 @@ static hipError_t launch_decode_rl(const DecodeParams& a, hipStream_t stream) {
                        dim3(NW * 64), 0, stream, a);
   }
   return hipGetLastError();
+}
+
+template <int D, int RMAX, bool LOCAL, int DS>
+static hipError_t launch_decode_rl(const DecodeParams& a, hipStream_t stream) {
+  if constexpr (RMAX == 4) {
+    if ((long long)a.P * a.Hkv * a.B <= kWideWorkgroups)
+      return launch_decode_nw<D, RMAX, 4, LOCAL, DS>(a, stream);
+  }
+  return launch_decode_nw<D, RMAX, kWaves<RMAX>, LOCAL, DS>(a, stream);
 }
 
 template <int D, int RMAX>
