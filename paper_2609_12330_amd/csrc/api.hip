@@ -701,7 +701,7 @@ namespace {
 // CUs on, the second producer, the two combines and the stored states cost more
 // than the idle CUs. Measured, split / one launch (us): 12 heads of 64, 4 x 512
 // of 2048 keys [192 tiles] 63.6 / 43.6; 32/8 heads of 128, 1024 of 8192 [256]
-// 282 / 244; 32 heads, 1024 of 32768 [256] 1003 / 996; but 512 of 16384 [128]
+// 282 / 237; 32 heads, 1024 of 32768 [256] 1003 / 968; but 512 of 16384 [128]
 // 290 / 411.
 constexpr long long kDiffPairTiles = 192;
 

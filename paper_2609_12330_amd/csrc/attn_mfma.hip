@@ -598,28 +598,37 @@ struct GroupTiles {
 // instruction; block i lies i KiB further both in memory and in LDS, so the
 // instruction offset serves both and only the lane offsets of K, whose chunk
 // permutation has a period of 16 rows, differ from block to block.
-template <int D, int NW>
+//
+// The waves that share a V stage are NV, at least the NW that share a K stage: the
+// two groups of a differential launch read the same values.
+template <int D, int NW, int NV>
 struct StageLoader {
   using G = TileGeom<D>;
   static constexpr int INSTS = 64 / G::RPI / NW;
+  static constexpr int VINSTS = 64 / G::RPI / NV;
+  static_assert(VINSTS >= 1, "whole blocks of V per wave");
   static constexpr int KPER = D == 128 ? 4 : 2;  // blocks of the K permutation's period
   static constexpr int NK = INSTS < KPER ? INSTS : KPER;
   __amdgpu_buffer_rsrc_t krs, vrs;
   unsigned koff[NK], voff;
-  int row0, slot;  // this lane's row in the wave's block 0, and its 16-byte slot
-  int wbase;       // byte offset of the wave's first block in a tile (scalar)
+  int row0, vrow0, slot;  // this lane's row in the wave's block 0 of K and V, its 16-byte slot
+  int wbase, vwbase;      // byte offset of the wave's first block in a tile (scalar)
 
-  __device__ __forceinline__ void init(const uint16_t* kh, const uint16_t* vh, int wave) {
+  // wave: index among the NW sharing a K stage; vwave: among the NV sharing a V stage.
+  __device__ __forceinline__ void init(const uint16_t* kh, const uint16_t* vh, int wave,
+                                       int vwave) {
     const int lane = threadIdx.x & 63;
     krs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(kh), (short)0, -1, 0x00020000);
     vrs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(vh), (short)0, -1, 0x00020000);
     wbase = wave * INSTS * 1024;
+    vwbase = vwave * VINSTS * 1024;
     row0 = wave * INSTS * G::RPI + lane / G::KCH;
+    vrow0 = vwave * VINSTS * G::RPI + lane / G::KCH;
     slot = lane % G::KCH;
 #pragma unroll
     for (int i = 0; i < NK; ++i)
       koff[i] = row0 * G::ROW + (slot ^ G::swz_k(row0 + i * G::RPI)) * 16;
-    voff = row0 * G::ROW + (slot ^ G::swz_v(row0)) * 16;
+    voff = vrow0 * G::ROW + (slot ^ G::swz_v(vrow0)) * 16;
   }
   // Block I of a whole tile.
   template <bool ISK, int I>
@@ -638,15 +647,16 @@ struct StageLoader {
   __device__ __forceinline__ void load(char* stage, int kb, int kend) const {
     const int nrows = kend - kb;
     if (nrows <= 0) return;  // a tile past the last one
-    char* l = stage + wbase;
+    constexpr int N = ISK ? INSTS : VINSTS;
+    char* l = stage + (ISK ? wbase : vwbase);
     const unsigned soff = (unsigned)kb * G::ROW;
     if (nrows >= 64) {
-      static_for<INSTS>([&](auto q) { block<ISK, decltype(q)::value>(l, soff); });
+      static_for<N>([&](auto q) { block<ISK, decltype(q)::value>(l, soff); });
     } else {
       // Ragged tile: rows past the run repeat its last row (masked later).
 #pragma unroll
-      for (int i = 0; i < INSTS; ++i) {
-        const int r = row0 + i * G::RPI;
+      for (int i = 0; i < N; ++i) {
+        const int r = (ISK ? row0 : vrow0) + i * G::RPI;
         const int c = slot ^ (ISK ? G::swz_k(r) : G::swz_v(r));
         const int off = min(r, nrows - 1) * G::ROW + c * 16;
         auto* d = (__attribute__((address_space(3))) void*)(l + i * 1024);
@@ -665,9 +675,9 @@ struct StageLoader {
 // values of tile u (V stage `vcur`, weights of its first half in pb on entry).
 // Meanwhile K of tile u + 2 and V of tile u + 1 land in the two stages nobody
 // reads during the step.
-template <int D, int NW>
+template <int D, int NW, int NV>
 __device__ __forceinline__ void pair_step(char* knext, char* kfree, char* vcur, char* vfree,
-                                          Rolling<D>& ro, const StageLoader<D, NW>& ld,
+                                          Rolling<D>& ro, const StageLoader<D, NW, NV>& ld,
                                           const TileAt& t0, const TileAt& t1, const TileAt& t2,
                                           bool second, int lim, int lo, int sinks, int h,
                                           floatx16& xa, floatx16& xb, uint32_t* pa, uint32_t* pb) {
@@ -707,8 +717,10 @@ enum Form {
 //
 // kDiffPair runs both branches of a differential layer in one launch: the
 // second branch's output stays in registers and LDS instead of going through o
-// between two launches. 32/8 heads of 128, 1024 causal: 52.5 -> 37.8 us, 4 x 1024:
-// 118.5 -> 108 us, 8 x 2048: 658 -> 647 us.
+// between two launches, and each V tile is staged once for both. 32/8 heads of
+// 128, 1024 causal: 52.5 -> 37.0 us, 4 x 1024: 118.5 -> 105.8 us; 32 heads, 1024 of
+// 32768 keys: 1003 us in two split branches, 999 in one launch, 968 with the
+// shared V stages.
 //
 // Occupancy target: two waves per SIMD (two workgroups of four waves per CU, four
 // of the streaming loop's two-wave ones, overlap each other's barrier and
@@ -898,12 +910,14 @@ void attn_mfma_kernel(MfmaParams a) {
     // first reads (they cannot alias) nor drains the LDS counter at every read
     // (it does with a flat direct-to-LDS load in flight).
     constexpr int STAGE = 2 * Geo::SUB;  // one group's bytes of a stage
+    // The two branches of a differential launch share the V stages.
+    constexpr int VGROUPS = F == kDiffPair ? 1 : GROUPS, NV = NW * GROUPS / VGROUPS;
     __shared__ __align__(1024) char sk0[GROUPS * STAGE], sk1[GROUPS * STAGE];
-    __shared__ __align__(1024) char sv0[GROUPS * STAGE], sv1[GROUPS * STAGE];
+    __shared__ __align__(1024) char sv0[VGROUPS * STAGE], sv1[VGROUPS * STAGE];
     char* const k0 = sk0 + grp * STAGE;
     char* const k1 = sk1 + grp * STAGE;
-    char* const v0 = sv0 + grp * STAGE;
-    char* const v1 = sv1 + grp * STAGE;
+    char* const v0 = sv0 + (VGROUPS > 1 ? grp * STAGE : 0);
+    char* const v1 = sv1 + (VGROUPS > 1 ? grp * STAGE : 0);
     // Tiles of this group, and the steps the workgroup's barriers count: those of
     // the first half of the tiles, which is never the shorter one.
     const int first_half = (ntiles + 1) / 2;
@@ -916,8 +930,8 @@ void attn_mfma_kernel(MfmaParams a) {
     uint32_t pa[8], pb[8];  // their weights
     Rolling<D> ro{kread, vread, qf, oacc, lsum, mref, c};
     if (ntiles > 0) {
-      StageLoader<D, NW> ld;
-      ld.init(kh, vh, wave);
+      StageLoader<D, NW, NV> ld;
+      ld.init(kh, vh, wave, F == kDiffPair ? wid : wave);
       TileAt t0 = gt.at(0), t1 = gt.at(1), t2;
       // Prologue: tile 0's K and V and tile 1's K; subtile 0's scores, then its
       // softmax beside subtile 1's scores. The second barrier orders those K reads
@@ -937,14 +951,14 @@ void attn_mfma_kernel(MfmaParams a) {
       for (int u = 0; u < steps; u += 2) {
         t2 = gt.at(u + 2);
         if (GROUPS == 1 || 2 * u + 1 < nsub)
-          pair_step<D, NW>(k1, k0, v0, v1, ro, ld, t0, t1, t2, 2 * u + 2 < nsub, lim, lo, tl.sinks,
+          pair_step<D, NW, NV>(k1, k0, v0, v1, ro, ld, t0, t1, t2, 2 * u + 2 < nsub, lim, lo, tl.sinks,
                            h, xa, xb, pa, pb);
         wait_tile_loads();
         __syncthreads();
         if (u + 1 >= steps) break;
         t0 = gt.at(u + 3);
         if (GROUPS == 1 || 2 * u + 3 < nsub)
-          pair_step<D, NW>(k0, k1, v1, v0, ro, ld, t1, t2, t0, 2 * u + 4 < nsub, lim, lo, tl.sinks,
+          pair_step<D, NW, NV>(k0, k1, v1, v0, ro, ld, t1, t2, t0, 2 * u + 4 < nsub, lim, lo, tl.sinks,
                            h, xa, xb, pa, pb);
         wait_tile_loads();
         __syncthreads();
