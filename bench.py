@@ -323,10 +323,13 @@ def measure(cfg, args, ef, wl, torch, dev, seed, cpu_budget, clock=None):
             if st:
                 raise RuntimeError(f"library error {st}")
     elif cfg.diff:
-        T = ef.splitkv_partition_size(B, Hq, Hkv, Sq, Skv, D,
-                                      0 if args.partition_size is None else args.partition_size)
+        T_req = args.partition_size or 0
+        wsb = int(ef.ef_diff_attention_workspace_size(B, Hq, Hkv, Sq, Skv, D, T_req))
+        # No workspace: one launch over both branches, one partition.
+        T = (ef.splitkv_partition_size(B, Hq, Hkv, Sq, Skv, D, T_req) if wsb > 0
+             else -(-Skv // 64) * 64)
         P = ef.splitkv_partitions(Sq, Skv, T)
-        wsb = max(256, int(ef.ef_diff_attention_workspace_size(B, Hq, Hkv, Sq, Skv, D, T)))
+        wsb = max(256, wsb)
         ws = torch.zeros(wsb, dtype=torch.uint8, device=dev)
 
         def step(i, ev=None):
@@ -344,16 +347,15 @@ def measure(cfg, args, ef, wl, torch, dev, seed, cpu_budget, clock=None):
                 raise RuntimeError(f"library error {st}")
 
         def produce(i):
-            """One branch's attention kernel alone, as ef_diff_attention launches it."""
+            """The attention kernel as ef_diff_attention launches it: both branches at once
+            in one partition, else one branch's producer."""
+            if P == 1:
+                return step(i)
             q, k, v = sets[i % nbuf]
             sh = torch.cuda.current_stream().cuda_stream
-            if P > 1:
-                st = ef.ef_attention_splitkv_partials(q.data_ptr(), k.data_ptr(), v.data_ptr(), B,
-                                                      Hq, Hkv, Sq, Skv, D, cfg.scale, cfg.causal,
-                                                      T, ws.data_ptr(), wsb, sh)
-            else:
-                st = ef.ef_attention_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(),
-                                         B, Hq, Hkv, Sq, Skv, D, cfg.scale, cfg.causal, sh)
+            st = ef.ef_attention_splitkv_partials(q.data_ptr(), k.data_ptr(), v.data_ptr(), B,
+                                                  Hq, Hkv, Sq, Skv, D, cfg.scale, cfg.causal,
+                                                  T, ws.data_ptr(), wsb, sh)
             if st:
                 raise RuntimeError(f"library error {st}")
     else:
@@ -457,8 +459,8 @@ def measure(cfg, args, ef, wl, torch, dev, seed, cpu_budget, clock=None):
         kernel = "attn_mfma" + ("_local" if cfg.local else "") + (
             ("_split_diff" if P > 1 else "_diff") if cfg.diff else "")
         src = source_hash("attn_mfma.hip", "ef_device.hpp")
-        # The differential layer launches the attention kernel once per branch.
-        flops = cfg.flops() // (2 if cfg.diff else 1)
+        # A split differential layer launches the producer once per branch.
+        flops = cfg.flops() // (2 if cfg.diff and P > 1 else 1)
         achieved = flops / (prod_avg * 1e-3) / 1e12
         roof = {"bound": "mfma", "achieved": round(achieved, 1), "peak": BF16_PEAK_TFLOPS,
                 "unit": "TFLOP/s", "frac": round(achieved / BF16_PEAK_TFLOPS, 4),

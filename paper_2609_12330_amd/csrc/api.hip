@@ -264,19 +264,22 @@ ef_status from_hip(hipError_t e) { return e == hipSuccess ? EF_OK : EF_ERR_HIP; 
 // chip holds waits for its longest chain of key tiles, which two groups halve;
 // with more, the rows of a 128-row workgroup make better use of each staged
 // tile. The two-group workgroup takes 128 KiB of LDS at D = 128 (one per CU) and
-// 64 KiB at D = 64 (two), so the line is one round of them; causal launches, whose
-// later workgroups are short, go a quarter past it. Measured, one group of 64 or
+// 64 KiB at D = 64 (two), so the line is one round of them; causal launches whose
+// workgroups get much shorter towards the end go a quarter past it (with a
+// window, or few queries over a long context, they do not: 8/2 heads of 64, 5 x
+// 865 of 4771 keys with a 792-key window [550] 25.6 / 26.4). Measured, one group of 64 or
 // 128 rows against two groups (us; 64-row tiles in brackets): D = 128 full,
 // 4096^2 x 4 heads [256] 66.9 / 47.6; causal 1024 of 8192
 // keys x 16 heads [256] 127.0 / 87.0, 32/8 heads 640 [320] 17.7 / 16.8, 777 [392]
 // 20.4 / 20.8, 16/4 heads 2048 [512] 39.5 / 41.8; 64 rows of 4000 keys x 32 [32]
 // 63.2 / 45.7; D = 64, 4 x 16 heads 384 full [384] 10.2 / 9.8, 16 heads 2048
 // causal [512] 29.7 / 23.6, 8 x 12 heads 384 full [576] 13.5 / 15.9.
-bool use_key_split(const Shape& s, int keys, int causal) {
+bool use_key_split(const Shape& s, const ef::KeyRuns& runs, int causal) {
   const long long R = (long long)(s.Hq / s.Hkv) * s.Sq;
   const long long tiles = (long long)s.B * s.Hkv * ((R + 63) / 64);
   const long long slots = s.D == 128 ? 256 : 512;
-  return keys > kTileKeys && tiles <= (causal ? slots + slots / 4 : slots);
+  const bool short_tail = causal && runs.window == 0 && s.Skv <= 2LL * s.Sq;
+  return runs.lv > kTileKeys && tiles <= (short_tail ? slots + slots / 4 : slots);
 }
 
 ef_status launch_mfma(const Shape& s, const void* q, const void* k, const void* v, float* o,
@@ -307,7 +310,7 @@ ef_status launch_mfma(const Shape& s, const void* q, const void* k, const void* 
     a.q2 = static_cast<const uint16_t*>(q2);
     a.k2 = static_cast<const uint16_t*>(k2);
     a.diff = *diff;
-  } else if (ws_m == nullptr && use_key_split(s, runs.lv, causal)) {
+  } else if (ws_m == nullptr && use_key_split(s, runs, causal)) {
     a.key_split = 1;
     a.bm = 64;
     a.mtiles = (a.R + 63) / 64;
@@ -705,6 +708,16 @@ namespace {
 // 290 / 411.
 constexpr long long kDiffPairTiles = 192;
 
+// And on short key axes, where two producers and two combines cost more than one
+// workgroup's chain of tiles, whatever the grid. Measured, split / one launch
+// (us): 6 x 4 heads of 128, 72 rows, 512 keys 25.0 / 21.0, 640 25.3 / 24.1, 1024
+// 27.9 / 32.5; 4 x 12 heads of 64, 128 rows, 640 keys 24.9 / 18.3, 1024 27.8 /
+// 24.4; 4 heads of 64, 64 rows, 640 keys 16.4 / 12.9, 1024 17.1 / 17.4; one row,
+// 32 heads of 128, 256 keys 11.4 / 10.7, 512 13.8 / 16.0.
+int diff_pair_keys(int D, long long R) {
+  return R <= kDecodeMaxRows ? 256 : D == 64 ? 896 : 640;
+}
+
 // Number of partitions ef_diff_attention uses (1 = single pass), or 0 for an
 // invalid shape or partition size.
 long long diff_partitions(const Shape& s, int partition_size, int* T_out) {
@@ -712,7 +725,9 @@ long long diff_partitions(const Shape& s, int partition_size, int* T_out) {
   if (partition_size < 0 || partition_size % kTileKeys != 0) return 0;
   if (s.rows() == 0 || s.Skv == 0) return 1;
   const long long R = (long long)(s.Hq / s.Hkv) * s.Sq;
-  if (partition_size == 0 && R > 64 && (long long)s.B * s.Hkv * ((R + 127) / 128) >= kDiffPairTiles)
+  if (partition_size == 0 &&
+      (s.Skv <= diff_pair_keys(s.D, R) ||
+       (R > 64 && (long long)s.B * s.Hkv * ((R + 127) / 128) >= kDiffPairTiles)))
     return 1;
   const int T = resolve_partition(s, s.Skv, partition_size, s.Skv);
   *T_out = T;

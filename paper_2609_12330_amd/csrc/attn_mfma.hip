@@ -401,8 +401,14 @@ __device__ __forceinline__ void static_for(F&& f) {
 //  - the maximum is only taken when a lane's sum of weights passes 2^8
 //    (soft_end), 57 vector instructions per 16 weights instead of 74;
 //  - tile loads keep one address register set for all tiles (StageLoader).
-// Together 61.5% busy: 8 x 8192^2 pairs of 32 heads 1064 -> 984 us, the
-// causal 2048 prefill of 4 x 32 heads 168.5 -> 156.5 us.
+// Together the matrix cores are busy 61.5-63% of the time: 8192 x 8192 keys,
+// 32/8 heads, 1064 -> 984 us; causal 4 x 2048, 168.5 -> 156.5 us; 1024 of 32768
+// keys, 32 heads, one branch 521 -> 490 us. Tried on top, not kept: fragments
+// read 4, 5 or 7 slots ahead (equal); eight waves sharing each tile (clock 1.89
+// GHz but 59.6% busy: 8192^2 920 us against 945, causal 4 x 2048 160 against 154);
+// 64 rows per wave, one wave per SIMD (half the fragment reads, 2.1 GHz, 51%
+// busy: 952 and 171 us); three or four stages per tile (25 us against 20 on a
+// 777-token prompt).
 template <int D>
 struct Rolling {
   using Geo = TileGeom<D>;

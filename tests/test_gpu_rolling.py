@@ -129,3 +129,28 @@ def test_diff_pair_key_counts(D, rows):
         bound = (1.0 - wl.DIFF_LAMBDA_INIT) * np.abs(g) * (dy / rms) * (1.0 + np.abs(y) / rms)
         err = np.abs(o.cpu().double().numpy() - ref)
         assert (err <= bound + 1e-6).all(), f"{what}: {(err / (bound + 1e-6)).max():.3f} of bound"
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_keys_at_the_end_of_the_largest_head(D):
+    """Tiles whose byte offset inside the head is just below 2^32 (the largest head the ABI
+    accepts): a window at its end against the same keys in a small tensor."""
+    n, tail, rows, window = (2**31 - 1) // D, 400, 130, 200
+    q, k, v = wl.make_shape_inputs(1, 1, 1, rows, tail, D, seed=5)
+    announce(f"last {tail} of {n} keys D{D}")
+    qd = q.cuda()
+    big = []
+    for t in (k, v):
+        b = torch.zeros(1, 1, n, D, dtype=torch.bfloat16, device="cuda")
+        b[:, :, n - tail:] = t.cuda()
+        big.append(b)
+    for sinks in (0, 3):
+        o = ef.attention_fwd(qd, *big, causal=True, window=window, sinks=sinks)
+        ks, vs = ([torch.cat([b[:, :, :sinks].cpu(), t], 2) for b, t in zip(big, (k, v))]
+                  if sinks else (k, v))
+        # The sink keys in front of the tail: rows see them whatever the window.
+        ref = oracle.attention_ref(f64(q), f64(ks), f64(vs), 1.0 / math.sqrt(D), True,
+                                   window=window, sinks=sinks)
+        torch.cuda.synchronize()
+        err = np.abs(o.cpu().double().numpy() - ref)
+        assert err.max() <= 1e-2, f"sinks {sinks}: max {err.max():.3e}"
