@@ -71,7 +71,6 @@ namespace {
 constexpr float kLazyThreshold = 8.f;  // base-2 headroom before the reference moves
 constexpr float kLazySum = 256.f;      // 2^8: a lane's weights whose sum is below are too
 constexpr float kNoRef = -3.402823466e+38f;  // rolling loop: no key seen yet (-FLT_MAX)
-constexpr unsigned kXcds = 8;                // accelerator dies of the chip
 
 // Geometry of K and V rows in LDS.
 template <int D>
@@ -756,13 +755,19 @@ void attn_mfma_kernel(MfmaParams a) {
   // chip's 8 XCDs round-robin by linear id; the id is remapped so that each XCD
   // receives a contiguous run of kv heads, and all row tiles of a head, which
   // read the same K/V, share one XCD's L2. Row tiles are visited last-first so
-  // causal tiles with the most keys start first.
+  // causal tiles with the most keys start first: head by head, or (a.interleave)
+  // over all heads of the XCD, which leaves only short tiles for the end.
   const unsigned nwg = gridDim.x * gridDim.y * gridDim.z;
   unsigned lin = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
   if (nwg % kXcds == 0) lin = (lin % kXcds) * (nwg / kXcds) + lin / kXcds;
-  const int mt = a.mtiles - 1 - (int)(lin % gridDim.x);
+  int mt = a.mtiles - 1 - (int)(lin % gridDim.x);
   const int p = (int)((lin / gridDim.x) % gridDim.y);
-  const int bh = (int)(lin / (gridDim.x * gridDim.y));
+  int bh = (int)(lin / (gridDim.x * gridDim.y));
+  if (a.interleave) {
+    const unsigned heads = gridDim.z / kXcds, wgs = nwg / kXcds;  // of one XCD
+    mt = a.mtiles - 1 - (int)(lin % wgs / heads);
+    bh = (int)(lin / wgs * heads + lin % wgs % heads);
+  }
   const int b = bh / a.Hkv, hkv = bh % a.Hkv;
 
   const size_t kvhead = ((size_t)b * a.Hkv + hkv) * (size_t)a.Skv * D;

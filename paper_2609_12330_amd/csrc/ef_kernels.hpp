@@ -67,6 +67,8 @@ constexpr int kCounterStride = 64;
 constexpr int kCounterSlots = 512;
 constexpr size_t kCounterRegionBytes = (size_t)kCounterSlots * kCounterStride * 4;
 
+constexpr unsigned kXcds = 8;  // accelerator dies of the chip
+
 // MFMA attention (single pass, or split producer when ws_m != nullptr).
 struct MfmaParams {
   const uint16_t* q;
@@ -85,6 +87,8 @@ struct MfmaParams {
   uint32_t qflip;  // 0x80008000 for a negative scale (q is negated), else 0
   int causal;
   KeyRuns runs;  // split mode: partitions cover the virtual key axis
+  int interleave;  // row tiles longest first over all heads of an XCD (B*Hkv a multiple of
+                   // kXcds, one partition), not head by head
   int key_split;  // 64-row tiles, two groups of waves over the halves of the key tiles
   // Differential attention, single pass only: with diff.gamma set this launch
   // forms both branches (q, k and q2, k2 over one v) and their mix.

@@ -154,3 +154,24 @@ def test_keys_at_the_end_of_the_largest_head(D):
         torch.cuda.synchronize()
         err = np.abs(o.cpu().double().numpy() - ref)
         assert err.max() <= 1e-2, f"sinks {sinks}: max {err.max():.3e}"
+
+
+@pytest.mark.parametrize("B,Hkv,Sq,Skv", [(1, 8, 200, 200), (2, 8, 140, 500), (3, 8, 130, 131),
+                                          (1, 16, 300, 1201), (8, 100, 70, 70)])
+def test_longest_first_order(B, Hkv, Sq, Skv):
+    """Causal launches over a multiple of eight kv heads visit their row tiles longest first
+    over an XCD's heads; every row of every head is compared (the last shape: one head per
+    batch row)."""
+    D, G = 64, 2
+    q, k, v = wl.make_shape_inputs(B, Hkv * G, Hkv, Sq, Skv, D, seed=Sq)
+    announce(f"longest first {B} {Hkv} {Sq} {Skv}")
+    bound = 2.0 ** -9 * float(v.float().abs().max()) + 1e-5
+    scale = 1.0 / math.sqrt(D)
+    o = ef.attention_fwd(q.cuda(), k.cuda(), v.cuda(), scale=scale, causal=True).cpu()
+    for b in range(B):
+        for h in (range(Hkv) if Hkv <= 16 else ((13 * b) % Hkv,)):
+            hq = slice(G * h, G * h + G)
+            ref = oracle.attention_ref(f64(q[b:b + 1, hq]), f64(k[b:b + 1, h:h + 1]),
+                                       f64(v[b:b + 1, h:h + 1]), scale, True)
+            err = np.abs(o[b:b + 1, hq].double().numpy() - ref)
+            assert err.max() <= bound, f"batch {b} kv head {h}: max {err.max():.3e}"
