@@ -236,6 +236,24 @@ __device__ __forceinline__ void subtile_scores(const char* kt, const int* kread,
                                                    sacc, 0, 0, 0);
 }
 
+// S^T of both 32-key subtiles of the 64-key tile at kt, their products alternating.
+template <int D>
+__device__ __forceinline__ void tile_scores(const char* kt, const int* kread, const bf16x8_t* qf,
+                                            floatx16& x0, floatx16& x1) {
+  constexpr int SUB = TileGeom<D>::SUB;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) x0[i] = x1[i] = 0.f;
+#pragma unroll
+  for (int s = 0; s < D / 16; ++s) {
+    const u32x4_t k0 = *reinterpret_cast<const u32x4_t*>(kt + kread[s]);
+    const u32x4_t k1 = *reinterpret_cast<const u32x4_t*>(kt + SUB + kread[s]);
+    x0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, k0), qf[s], x0, 0,
+                                                0, 0);
+    x1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, k1), qf[s], x1, 0,
+                                                0, 0);
+  }
+}
+
 // Softmax and value steps of the streaming loop's 32-key tiles.
 template <int D>
 struct Tile {
@@ -504,12 +522,25 @@ struct Rolling {
       }
     });
   }
+  // The first tile's scores (x0, x1) set the reference to the row's maximum over
+  // its 64 keys, and x0's weights are formed. Taken over the first subtile alone,
+  // the reference was below more rows' largest score, whose weight then is no
+  // longer exactly 1 but rounded to bf16: the error against 64 bits of 64 keys at
+  // D = 64 was 1.50e-3 instead of 1.33e-3, of 384 keys 1.62e-3 instead of 1.60e-3.
+  __device__ __forceinline__ void start(const floatx16& x0, const floatx16& x1, uint32_t* pout) {
+    float tmax = fmaxf(x0[0], x1[0]);
+#pragma unroll
+    for (int i = 1; i < 16; ++i) tmax = fmaxf(tmax, fmaxf(x0[i], x1[i]));
+    mref = fmaxf(mref, max_with_other_half(tmax) * c);
+    Soft f;
+    soft_slot<0, 1>(f, x0, pout);
+    lsum = (f.ps[0] + f.ps[1]) + (f.ps[2] + f.ps[3]);
+  }
   // A lane's weights are all at most 2^8 when their sum is, and then the
-  // reference stays. Otherwise (the first visible keys of a row, or a larger
-  // score) the reference moves up to the subtile's maximum, the carried sum and
-  // value are rescaled and the weights formed again.
-  __device__ __forceinline__ void soft_end(Soft& f, const floatx16& x, uint32_t* pout,
-                                           bool values) {
+  // reference stays. Otherwise (a row's first visible keys past its first tile, or
+  // a larger score) the reference moves up to the subtile's maximum, the carried
+  // sum and value are rescaled and the weights formed again.
+  __device__ __forceinline__ void soft_end(Soft& f, const floatx16& x, uint32_t* pout) {
     float sum = (f.ps[0] + f.ps[1]) + (f.ps[2] + f.ps[3]);
     if (__builtin_amdgcn_ballot_w64(!(sum <= kLazySum))) {
       float tmax = fmaxf(x[0], x[1]);
@@ -520,12 +551,10 @@ struct Rolling {
       mref = fmaxf(mref, cand);
       const float rs = exp2_fast(old - mref);  // 1 where the reference stayed
       lsum *= rs;
-      if (values) {
 #pragma unroll
-        for (int i = 0; i < DT; ++i)
+      for (int i = 0; i < DT; ++i)
 #pragma unroll
-          for (int jj = 0; jj < 16; ++jj) oacc[i][jj] *= rs;
-      }
+        for (int jj = 0; jj < 16; ++jj) oacc[i][jj] *= rs;
       soft_slot<0, 1>(f, x, pout);
       sum = (f.ps[0] + f.ps[1]) + (f.ps[2] + f.ps[3]);
     }
@@ -533,35 +562,33 @@ struct Rolling {
   }
 
   // Subtile softmax of x into pout, the next subtile's scores into y (K subtile
-  // at kt) and, with VALUES, the values of the previous subtile (V subtile at
-  // vt, weights pin). fr: fragments; with CARRY_IN the first PF are already in
-  // fr[0..PF), with CARRY_OUT the next subtile's first PF are left there.
-  template <bool VALUES, bool CARRY_IN, bool CARRY_OUT>
+  // at kt) and the values of the previous subtile (V subtile at vt, weights pin).
+  // With CARRY_IN the first PF fragments are in carry, with CARRY_OUT the next
+  // subtile's first PF are left there.
+  template <bool CARRY_IN, bool CARRY_OUT>
   __device__ __forceinline__ void subtile(const floatx16& x, floatx16& y, const uint32_t* pin,
                                           uint32_t* pout, const char* kt, const char* vt,
                                           const char* kt2, const char* vt2, u32x4_t* carry) {
     u32x4_t fr[SLOTS];
     static_for<PF>([&](auto i) {
       constexpr int I = decltype(i)::value;
-      if constexpr (VALUES || is_score(I)) {
-        if constexpr (CARRY_IN) fr[I] = carry[I];
-        else fr[I] = fragment<I>(kt, vt);
-      }
+      if constexpr (CARRY_IN) fr[I] = carry[I];
+      else fr[I] = fragment<I>(kt, vt);
     });
     __builtin_amdgcn_sched_barrier(0);
     Soft f;
     static_for<SLOTS>([&](auto i) {
       constexpr int I = decltype(i)::value;
       if constexpr (I + PF < SLOTS) {
-        if constexpr (VALUES || is_score(I + PF)) fr[I + PF] = fragment<I + PF>(kt, vt);
+        fr[I + PF] = fragment<I + PF>(kt, vt);
       } else if constexpr (CARRY_OUT) {
         carry[I + PF - SLOTS] = fragment<I + PF - SLOTS>(kt2, vt2);
       }
-      if constexpr (VALUES || is_score(I)) product<I>(fr[I], y, pin);
+      product<I>(fr[I], y, pin);
       soft_slot<I, SLOTS>(f, x, pout);
       __builtin_amdgcn_sched_barrier(0);
     });
-    soft_end(f, x, pout, VALUES);
+    soft_end(f, x, pout);
   }
 
   // Values of the last subtile.
@@ -692,12 +719,11 @@ __device__ __forceinline__ void pair_step(char* knext, char* kfree, char* vcur, 
   ld.template load<true>(kfree, t2.base, t2.end);
   ld.template load<false>(vfree, t1.base, t1.end);
   if (t0.masked) mask_scores(xa, t0.base + 32, t0.end, lim, lo, sinks, h);
-  ro.template subtile<true, false, true>(xa, xb, pb, pa, knext, vcur, knext + SUB,
-                                         vcur + SUB, carry);
+  ro.template subtile<false, true>(xa, xb, pb, pa, knext, vcur, knext + SUB, vcur + SUB, carry);
   if (second) {
     if (t1.masked) mask_scores(xb, t1.base, t1.end, lim, lo, sinks, h);
-    ro.template subtile<true, true, false>(xb, xa, pa, pb, knext + SUB, vcur + SUB, nullptr,
-                                           nullptr, carry);
+    ro.template subtile<true, false>(xb, xa, pa, pb, knext + SUB, vcur + SUB, nullptr, nullptr,
+                                     carry);
   }
 }
 
@@ -944,19 +970,22 @@ void attn_mfma_kernel(MfmaParams a) {
       StageLoader<D, NW, NV> ld;
       ld.init(kh, vh, wave, F == kDiffPair ? wid : wave);
       TileAt t0 = gt.at(0), t1 = gt.at(1), t2;
-      // Prologue: tile 0's K and V and tile 1's K; subtile 0's scores, then its
-      // softmax beside subtile 1's scores. The second barrier orders those K reads
-      // before stage 0 is rewritten by the first step.
+      // Prologue: tile 0's K and V and tile 1's K; tile 0's scores, then subtile 0's
+      // softmax. The second barrier orders those K reads before stage 0 is rewritten
+      // by the first step.
       ld.template load<true>(k0, t0.base, t0.end);
       ld.template load<false>(v0, t0.base, t0.end);
       ld.template load<true>(k1, t1.base, t1.end);
       wait_tile_loads();
       __syncthreads();
       if (GROUPS == 1 || nsub > 0) {
-        subtile_scores<D>(k0, kread, qf, xb);
-        if (t0.masked) mask_scores(xb, t0.base, t0.end, lim, lo, tl.sinks, h);
-        ro.template subtile<false, false, false>(xb, xa, nullptr, pb, k0 + Geo::SUB, nullptr,
-                                                 nullptr, nullptr, nullptr);
+        tile_scores<D>(k0, kread, qf, xb, xa);
+        if (t0.masked) {
+          mask_scores(xb, t0.base, t0.end, lim, lo, tl.sinks, h);
+          mask_scores(xa, t0.base + 32, t0.end, lim, lo, tl.sinks, h);
+          t0.masked = false;  // both halves are
+        }
+        ro.start(xb, xa, pb);
       }
       __syncthreads();
       for (int u = 0; u < steps; u += 2) {

@@ -175,3 +175,38 @@ def test_longest_first_order(B, Hkv, Sq, Skv):
                                        f64(v[b:b + 1, h:h + 1]), scale, True)
             err = np.abs(o[b:b + 1, hq].double().numpy() - ref)
             assert err.max() <= bound, f"batch {b} kv head {h}: max {err.max():.3e}"
+
+
+def _rounded(q, k, v, scale, causal):
+    """The attention of one kv head in float64, but for the rounding of each weight to bf16
+    against the row's maximum over the keys of its first tile (64)."""
+    s = torch.from_numpy(f64(q) @ f64(k).swapaxes(-1, -2)) * (scale / math.log(2.0))
+    sq, skv = s.shape[-2:]
+    if causal:
+        s.masked_fill_(torch.ones(sq, skv).tril(skv - sq) == 0, -math.inf)
+    w = torch.exp2(s - s[..., :64].max(-1, keepdim=True).values)
+    assert float(w.max()) < 2.0 ** 8 / 16  # no 16 weights pass 2^8: the reference stays
+    return ((w.float().bfloat16().double() @ v.double()) / w.sum(-1, keepdim=True)).numpy()
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("H,rows,n", [(1, 64, 64), (3, 130, 47), (700, 64, 200), (700, 130, 97)])
+def test_reference_of_the_first_tile(D, H, rows, n):
+    """Weights are formed against the maximum of a row's first 64 keys, so that of a short row's
+    largest weight nothing is lost in bf16. Against the same rounding in float64 what is left is
+    fp32 arithmetic, and the few weights whose fp32 value (relative error below 2e-6) falls on the
+    other side of a rounding boundary (share 2e-6 / 2^-9, an error of 2^-9 each, so
+    sqrt(1e-3) 2^-9 = 6e-5 of the 2-norm). A reference 2^0.5 off gives 1.5e-3."""
+    q, k, v = wl.make_shape_inputs(1, H, H, rows, n, D, seed=n)
+    scale = 1.0 / math.sqrt(D)
+    for causal in (False, True):
+        if causal and rows > n:
+            continue
+        what = f"first tile {H} heads rows {rows} keys {n} D{D} {causal}"
+        announce(what)
+        o = ef.attention_fwd(q.cuda(), k.cuda(), v.cuda(), scale=scale, causal=causal)
+        for h in {0, H // 2, H - 1}:
+            ref = _rounded(q[:, h], k[:, h], v[:, h], scale, causal)
+            err = o[:, h].cpu().double().numpy() - ref
+            rel = np.linalg.norm(err) / np.linalg.norm(ref)
+            assert rel <= 2e-4, f"{what} head {h}: {rel:.2e}"
