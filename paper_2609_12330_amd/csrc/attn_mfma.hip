@@ -71,6 +71,7 @@ namespace {
 constexpr float kLazyThreshold = 8.f;  // base-2 headroom before the reference moves
 constexpr float kLazySum = 256.f;      // 2^8: a lane's weights whose sum is below are too
 constexpr float kNoRef = -3.402823466e+38f;  // rolling loop: no key seen yet (-FLT_MAX)
+constexpr float kRenewDepth = 16.f;  // a renewed reference lies at most this far below the top
 
 // Geometry of K and V rows in LDS.
 template <int D>
@@ -528,13 +529,37 @@ struct Rolling {
   // longer exactly 1 but rounded to bf16: the error against 64 bits of 64 keys at
   // D = 64 was 1.50e-3 instead of 1.33e-3, of 384 keys 1.62e-3 instead of 1.60e-3.
   __device__ __forceinline__ void start(const floatx16& x0, const floatx16& x1, uint32_t* pout) {
+    mref = fmaxf(mref, tile_max(x0, x1));
+    Soft f;
+    soft_slot<0, 1>(f, x0, pout);
+    lsum += (f.ps[0] + f.ps[1]) + (f.ps[2] + f.ps[3]);
+  }
+  // A tile that renews the reference: it moves to the maximum of the tile, down as
+  // well as up, and the carried sum and value move with it. Down at most
+  // kRenewDepth below the largest so far (`top`), so that they grow by 2^kRenewDepth
+  // at most; weights further below round to nothing that matters.
+  __device__ __forceinline__ void renew(float& top, const floatx16& x0, const floatx16& x1,
+                                        uint32_t* pout) {
+    const float old = mref;
+    top = fmaxf(top, old);
+    mref = fmaxf(top - kRenewDepth, tile_max(x0, x1));  // kNoRef - kRenewDepth is kNoRef
+    rescale(exp2_fast(old - mref));
+    start(x0, x1, pout);
+  }
+  // Largest score of a row in a 64-key tile, base-2 units.
+  __device__ __forceinline__ float tile_max(const floatx16& x0, const floatx16& x1) const {
     float tmax = fmaxf(x0[0], x1[0]);
 #pragma unroll
     for (int i = 1; i < 16; ++i) tmax = fmaxf(tmax, fmaxf(x0[i], x1[i]));
-    mref = fmaxf(mref, max_with_other_half(tmax) * c);
-    Soft f;
-    soft_slot<0, 1>(f, x0, pout);
-    lsum = (f.ps[0] + f.ps[1]) + (f.ps[2] + f.ps[3]);
+    return max_with_other_half(tmax) * c;
+  }
+  // Moves the carried sum and value to another reference.
+  __device__ __forceinline__ void rescale(float rs) {
+    lsum *= rs;
+#pragma unroll
+    for (int i = 0; i < DT; ++i)
+#pragma unroll
+      for (int jj = 0; jj < 16; ++jj) oacc[i][jj] *= rs;
   }
   // A lane's weights are all at most 2^8 when their sum is, and then the
   // reference stays. Otherwise (a row's first visible keys past its first tile, or
@@ -549,12 +574,7 @@ struct Rolling {
       const float cand = max_with_other_half(tmax) * c;
       const float old = mref;
       mref = fmaxf(mref, cand);
-      const float rs = exp2_fast(old - mref);  // 1 where the reference stayed
-      lsum *= rs;
-#pragma unroll
-      for (int i = 0; i < DT; ++i)
-#pragma unroll
-        for (int jj = 0; jj < 16; ++jj) oacc[i][jj] *= rs;
+      rescale(exp2_fast(old - mref));  // by 1 where the reference stayed
       soft_slot<0, 1>(f, x, pout);
       sum = (f.ps[0] + f.ps[1]) + (f.ps[2] + f.ps[3]);
     }
@@ -591,6 +611,23 @@ struct Rolling {
     soft_end(f, x, pout);
   }
 
+  // The products of a subtile alone.
+  __device__ __forceinline__ void products(floatx16& y, const uint32_t* pin, const char* kt,
+                                           const char* vt) {
+    u32x4_t fr[SLOTS];
+    static_for<PF>([&](auto i) {
+      constexpr int I = decltype(i)::value;
+      fr[I] = fragment<I>(kt, vt);
+    });
+    __builtin_amdgcn_sched_barrier(0);
+    static_for<SLOTS>([&](auto i) {
+      constexpr int I = decltype(i)::value;
+      if constexpr (I + PF < SLOTS) fr[I + PF] = fragment<I + PF>(kt, vt);
+      product<I>(fr[I], y, pin);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  }
+
   // Values of the last subtile.
   __device__ __forceinline__ void last_values(const uint32_t* pin, const char* vt) {
     static_for<SLOTS>([&](auto i) {
@@ -603,20 +640,21 @@ struct Rolling {
   }
 };
 
-// One 64-key tile of the list: its first key, the end of its run, and whether
-// some key of it is hidden from some row of the workgroup.
+// One 64-key tile of the list: its first key, the end of its run, whether some
+// key of it is hidden from some row of the workgroup, and whether it renews the
+// reference.
 struct TileAt {
   int base, end;
-  bool masked;
+  bool masked, renews;
 };
 
 // The tiles [first, first + n) of the list that one group of waves walks.
 struct GroupTiles {
   const TileList<64>& tl;
   int first, n;
-  __device__ __forceinline__ TileAt at(int t) const {
-    if (t >= n) return {0, 0, false};  // nothing to load
-    return {tl.base(first + t), tl.end(first + t), tl.masked(first + t)};
+  __device__ __forceinline__ TileAt at(int t, bool renews) const {
+    if (t >= n) return {0, 0, false, false};  // nothing to load
+    return {tl.base(first + t), tl.end(first + t), tl.masked(first + t), renews};
   }
   // 32-key subtiles; the list's last tile may end within its first half.
   __device__ __forceinline__ int subtiles() const {
@@ -706,13 +744,15 @@ struct StageLoader {
 // (xb, if `second`), beside the scores of tile u + 1 (K stage `knext`) and the
 // values of tile u (V stage `vcur`, weights of its first half in pb on entry).
 // Meanwhile K of tile u + 2 and V of tile u + 1 land in the two stages nobody
-// reads during the step.
-template <int D, int NW, int NV>
+// reads during the step. With RENEW a tile u + 1 may renew the reference: then its
+// weights wait for both halves of its scores and all values of tile u.
+template <int D, int NW, int NV, bool RENEW>
 __device__ __forceinline__ void pair_step(char* knext, char* kfree, char* vcur, char* vfree,
                                           Rolling<D>& ro, const StageLoader<D, NW, NV>& ld,
-                                          const TileAt& t0, const TileAt& t1, const TileAt& t2,
-                                          bool second, int lim, int lo, int sinks, int h,
-                                          floatx16& xa, floatx16& xb, uint32_t* pa, uint32_t* pb) {
+                                          const TileAt& t0, TileAt& t1, const TileAt& t2,
+                                          bool second, float& top, int lim, int lo, int sinks,
+                                          int h, floatx16& xa, floatx16& xb, uint32_t* pa,
+                                          uint32_t* pb) {
   using R = Rolling<D>;
   constexpr int SUB = TileGeom<D>::SUB;
   u32x4_t carry[R::PF];
@@ -720,10 +760,20 @@ __device__ __forceinline__ void pair_step(char* knext, char* kfree, char* vcur, 
   ld.template load<false>(vfree, t1.base, t1.end);
   if (t0.masked) mask_scores(xa, t0.base + 32, t0.end, lim, lo, sinks, h);
   ro.template subtile<false, true>(xa, xb, pb, pa, knext, vcur, knext + SUB, vcur + SUB, carry);
-  if (second) {
+  const bool renews = RENEW && __builtin_expect(t1.renews, 0);
+  if (second && !renews) {
     if (t1.masked) mask_scores(xb, t1.base, t1.end, lim, lo, sinks, h);
     ro.template subtile<true, false>(xb, xa, pa, pb, knext + SUB, vcur + SUB, nullptr, nullptr,
                                      carry);
+  }
+  if (renews) {
+    ro.products(xa, pa, knext + SUB, vcur + SUB);
+    if (t1.masked) {
+      mask_scores(xb, t1.base, t1.end, lim, lo, sinks, h);
+      mask_scores(xa, t1.base + 32, t1.end, lim, lo, sinks, h);
+      t1.masked = false;  // both halves are
+    }
+    ro.renew(top, xb, xa, pb);
   }
 }
 
@@ -734,6 +784,7 @@ enum Form {
   kKeySplit,  // rolling loop, two groups of waves over the two halves of the key tiles
   kDiffPair,  // rolling loop, two groups of waves over the two branches of a
               // differential layer
+  kDiffRenew,  // kDiffPair whose rows renew their reference every a.renew tiles
 };
 
 // NW waves (of 32 query rows each) per group; the two-group forms hold two
@@ -753,17 +804,30 @@ enum Form {
 // 32768 keys: 1003 us in two split branches, 999 in one launch, 968 with the
 // shared V stages.
 //
+// kDiffRenew is kDiffPair where the launch takes the place of a split call: every
+// a.renew key tiles, the tiles of one of the split's partitions, a row's reference
+// starts again at the maximum of a 64-key tile, as each partition's would, so the
+// weights are rounded to bf16 as the split rounds them. The renewal stands behind
+// the step in a block of its own: as an else of the step's second half it cost 87
+// spilled registers, inside the second half 4% on every step. It costs a step of
+// its own, 1-1.5 us: 32 heads, 1024 of 32768 keys, every 256 tiles 986 us without,
+// 992 with it; 32/8 heads of 64, 768 of 3000 keys, every 32 tiles 55.7, 57.9; 12
+// heads of 64, 128 of 640 keys, every tile 17.6, 22.2.
+//
 // Occupancy target: two waves per SIMD (two workgroups of four waves per CU, four
 // of the streaming loop's two-wave ones, overlap each other's barrier and
-// latency stalls; a workgroup of eight waves has both on its own); the
-// four-wave two-group form and the two-wave workgroup of the rolling loop serve
+// latency stalls; a workgroup of eight waves has both on its own), three at D = 64
+// where the registers allow; the four-wave two-group form and the two-wave workgroup of the rolling loop serve
 // grids too small for that.
 template <int D, int NW, Form F>
 __global__ __launch_bounds__(NW * 64 * (F >= kKeySplit ? 2 : 1))
-__attribute__((amdgpu_waves_per_eu(NW == 2 && F != kStream ? 1 : D == 64 ? 3 : 2)))
+__attribute__((amdgpu_waves_per_eu(NW == 2 && F != kStream         ? 1
+                                   : D == 64 && F < kKeySplit ? 3
+                                                              : 2)))
 void attn_mfma_kernel(MfmaParams a) {
   using Geo = TileGeom<D>;
   constexpr bool STREAM = F == kStream;
+  constexpr bool DIFF = F >= kDiffPair, RENEW = F == kDiffRenew;
   constexpr int GROUPS = F >= kKeySplit ? 2 : 1;
   constexpr int KSTEPS = D / 16;
   constexpr int DT = D / 32;
@@ -797,7 +861,7 @@ void attn_mfma_kernel(MfmaParams a) {
   const int b = bh / a.Hkv, hkv = bh % a.Hkv;
 
   const size_t kvhead = ((size_t)b * a.Hkv + hkv) * (size_t)a.Skv * D;
-  const uint16_t* kh = (F == kDiffPair && grp ? a.k2 : a.k) + kvhead;
+  const uint16_t* kh = (DIFF && grp ? a.k2 : a.k) + kvhead;
   const uint16_t* vh = a.v + kvhead;
 
   // This lane's query row.
@@ -846,7 +910,8 @@ void attn_mfma_kernel(MfmaParams a) {
   // Q^T fragments (B operand): lane holds q[row][16*s + 8*h .. +8].
   bf16x8_t qf[KSTEPS];
   {
-    const u32x4_t* qp = reinterpret_cast<const u32x4_t*>((F == kDiffPair && grp ? a.q2 : a.q) + orow * D);
+    const u32x4_t* qp =
+        reinterpret_cast<const u32x4_t*>((DIFF && grp ? a.q2 : a.q) + orow * D);
     const u32x4_t zero = {0u, 0u, 0u, 0u};
 #pragma unroll
     for (int s = 0; s < KSTEPS; ++s) {
@@ -948,7 +1013,7 @@ void attn_mfma_kernel(MfmaParams a) {
     // (it does with a flat direct-to-LDS load in flight).
     constexpr int STAGE = 2 * Geo::SUB;  // one group's bytes of a stage
     // The two branches of a differential launch share the V stages.
-    constexpr int VGROUPS = F == kDiffPair ? 1 : GROUPS, NV = NW * GROUPS / VGROUPS;
+    constexpr int VGROUPS = DIFF ? 1 : GROUPS, NV = NW * GROUPS / VGROUPS;
     __shared__ __align__(1024) char sk0[GROUPS * STAGE], sk1[GROUPS * STAGE];
     __shared__ __align__(1024) char sv0[VGROUPS * STAGE], sv1[VGROUPS * STAGE];
     char* const k0 = sk0 + grp * STAGE;
@@ -968,8 +1033,15 @@ void attn_mfma_kernel(MfmaParams a) {
     Rolling<D> ro{kread, vread, qf, oacc, lsum, mref, c};
     if (ntiles > 0) {
       StageLoader<D, NW, NV> ld;
-      ld.init(kh, vh, wave, F == kDiffPair ? wid : wave);
-      TileAt t0 = gt.at(0), t1 = gt.at(1), t2;
+      ld.init(kh, vh, wave, DIFF ? wid : wave);
+      int due = RENEW ? a.renew : 0;  // tiles until the next one that renews
+      float top = kNoRef;
+      auto tile = [&](int t) {  // t = 1, 2, 3, ...
+        const bool renews = RENEW && --due == 0;
+        if (renews) due = a.renew;
+        return gt.at(t, renews);
+      };
+      TileAt t0 = gt.at(0, false), t1 = tile(1), t2;
       // Prologue: tile 0's K and V and tile 1's K; tile 0's scores, then subtile 0's
       // softmax. The second barrier orders those K reads before stage 0 is rewritten
       // by the first step.
@@ -989,17 +1061,17 @@ void attn_mfma_kernel(MfmaParams a) {
       }
       __syncthreads();
       for (int u = 0; u < steps; u += 2) {
-        t2 = gt.at(u + 2);
+        t2 = tile(u + 2);
         if (GROUPS == 1 || 2 * u + 1 < nsub)
-          pair_step<D, NW, NV>(k1, k0, v0, v1, ro, ld, t0, t1, t2, 2 * u + 2 < nsub, lim, lo, tl.sinks,
-                           h, xa, xb, pa, pb);
+          pair_step<D, NW, NV, RENEW>(k1, k0, v0, v1, ro, ld, t0, t1, t2, 2 * u + 2 < nsub, top,
+                                      lim, lo, tl.sinks, h, xa, xb, pa, pb);
         wait_tile_loads();
         __syncthreads();
         if (u + 1 >= steps) break;
-        t0 = gt.at(u + 3);
+        t0 = tile(u + 3);
         if (GROUPS == 1 || 2 * u + 3 < nsub)
-          pair_step<D, NW, NV>(k0, k1, v1, v0, ro, ld, t1, t2, t0, 2 * u + 4 < nsub, lim, lo, tl.sinks,
-                           h, xa, xb, pa, pb);
+          pair_step<D, NW, NV, RENEW>(k0, k1, v1, v0, ro, ld, t1, t2, t0, 2 * u + 4 < nsub, top,
+                                      lim, lo, tl.sinks, h, xa, xb, pa, pb);
         wait_tile_loads();
         __syncthreads();
         t1 = t0;
@@ -1038,7 +1110,7 @@ void attn_mfma_kernel(MfmaParams a) {
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             x[e] = grp ? oacc[i][4 * q4 + e] : oacc[HT + i][4 * q4 + e];
-            if constexpr (F == kDiffPair) x[e] *= inv;
+            if constexpr (DIFF) x[e] *= inv;
           }
           out[(i * 4 + q4) * 64] = make_float4(x[0], x[1], x[2], x[3]);
         }
@@ -1111,9 +1183,13 @@ hipError_t launch_one(const MfmaParams& a, hipStream_t stream) {
 
 template <int D>
 hipError_t launch_d(const MfmaParams& a, hipStream_t stream) {
-  if (a.diff.gamma != nullptr)
+  if (a.diff.gamma != nullptr) {
+    if (a.renew > 0)
+      return a.bm == 64 ? launch_one<D, 2, kDiffRenew>(a, stream)
+                        : launch_one<D, 4, kDiffRenew>(a, stream);
     return a.bm == 64 ? launch_one<D, 2, kDiffPair>(a, stream)
                       : launch_one<D, 4, kDiffPair>(a, stream);
+  }
   if (a.key_split) return launch_one<D, 2, kKeySplit>(a, stream);
   if (a.bm == 128) return launch_one<D, 4, kRolling>(a, stream);
   // The split producer with one 64-row tile per kv head (decode shapes) streams:

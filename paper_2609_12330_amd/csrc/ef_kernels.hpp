@@ -94,6 +94,7 @@ struct MfmaParams {
   // forms both branches (q, k and q2, k2 over one v) and their mix.
   const uint16_t* q2;
   const uint16_t* k2;
+  int renew;  // key tiles between renewals of a row's reference, 0: none
   DiffParams diff;
 };
 

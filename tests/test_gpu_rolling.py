@@ -210,3 +210,97 @@ def test_reference_of_the_first_tile(D, H, rows, n):
             err = o[:, h].cpu().double().numpy() - ref
             rel = np.linalg.norm(err) / np.linalg.norm(ref)
             assert rel <= 2e-4, f"{what} head {h}: {rel:.2e}"
+
+
+def _moving(order, sign, n, rows, D, heads, seed):
+    """q, k, v with scaled scores that follow `order` along the key axis, up to about 24."""
+    q, k, v = wl.make_shape_inputs(1, 2 * heads, heads, rows, n, D, seed=seed)
+    j = torch.arange(n, dtype=torch.float32)
+    ramp = {"rising": j / n, "falling": 1.0 - j / n,
+            "spikes": (j % 97 == 96).float()}[order][None, None, :, None]
+    u = torch.randn(D, generator=torch.Generator().manual_seed(3))
+    u = u / u.norm()
+    q = (q.float() - (q.float() @ u)[..., None] * u + 6.0 * u).to(torch.bfloat16)
+    k = (k.float() + sign * 4.0 * math.sqrt(D) * ramp * u).to(torch.bfloat16)
+    return q, k, v
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("rows", [20, 70])  # two-wave and four-wave workgroups
+@pytest.mark.parametrize("order", ["rising", "falling", "spikes"])
+def test_reference_moves_plain(D, rows, order):
+    """As test_reference_moves, through the plain form (many heads; three are compared)."""
+    H, n = 700, 419
+    q, k, v = _moving(order, 1.0, n, rows, D, H, 7)
+    scale = 1.0 / math.sqrt(D)
+    bound = 2.0 ** -9 * float(v.float().abs().max()) + 1e-5
+    for causal in (False, True):
+        what = f"{order} {H} heads rows {rows} D{D} {causal}"
+        announce(what)
+        o = ef.attention_fwd(q.cuda(), k.cuda(), v.cuda(), scale=scale, causal=causal).cpu()
+        for h in (0, 311, H - 1):
+            hq = slice(2 * h, 2 * h + 2)
+            ref = oracle.attention_ref(f64(q[:, hq]), f64(k[:, h:h + 1]), f64(v[:, h:h + 1]),
+                                       scale, causal)
+            err = np.abs(o[:, hq].double().numpy() - ref)
+            assert err.max() <= bound, f"{what} head {h}: max {err.max():.3e}"
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("rows", [24, 130])
+@pytest.mark.parametrize("order", ["rising", "falling", "spikes"])
+@pytest.mark.parametrize("partition", [0, 384])  # with and without renewals of the reference
+def test_reference_moves_diff(D, rows, order, partition):
+    """Both branches in one launch over scores that move a branch's reference further than a
+    renewal may take it down. Bound as in test_diff_pair_key_counts."""
+    n = 379
+    q1, k1, v = _moving(order, 1.0, n, rows, D, 1, 7)
+    q2, k2, _ = _moving("falling" if order == "rising" else "rising", 1.0, n, rows, D, 1, 9)
+    lam, gamma = wl.make_diff_inputs(1, 2, 1, 1, 1, D, seed=1)[5:]
+    scale = 1.0 / math.sqrt(D)
+    assert ef.ef_diff_attention_workspace_size(1, 2, 1, rows, n, D, partition) == 0  # one launch
+    for causal in (False, True):
+        what = f"diff {order} rows {rows} D{D} T{partition} {causal}"
+        announce(what)
+        o = ef.diff_attention(*(t.cuda() for t in (q1, q2, k1, k2, v) + tuple(lam) + (gamma,)),
+                              wl.DIFF_LAMBDA_INIT, wl.DIFF_EPS, scale=scale, causal=causal,
+                              partition_size=partition)
+        a1 = oracle.attention_ref(f64(q1), f64(k1), f64(v), scale, causal)
+        a2 = oracle.attention_ref(f64(q2), f64(k2), f64(v), scale, causal)
+        l64 = [t.double().numpy() for t in lam]
+        mix = np.exp(l64[0] @ l64[1]) - np.exp(l64[2] @ l64[3]) + wl.DIFF_LAMBDA_INIT
+        y = a1 - mix * a2
+        rms = np.sqrt((y * y).mean(-1, keepdims=True) + wl.DIFF_EPS)
+        g = np.abs(gamma.double().numpy()) * (1.0 - wl.DIFF_LAMBDA_INIT)
+        dy = 2.0 ** -9 * float(v.float().abs().max()) * (1.0 + abs(mix))
+        ref = np.sign(gamma.double().numpy()) * g * y / rms
+        err = np.abs(o.cpu().double().numpy() - ref)
+        bound = g * (dy / rms) * (1.0 + np.abs(y) / rms) + 1e-6
+        assert (err <= bound).all(), f"{what}: {(err / bound).max():.3f} of bound"
+
+
+# B, Hq, Hkv, Sq, Skv, D: layers whose key axis the model would cut into 2 to 10 partitions.
+ONE_LAUNCH = [(2, 8, 8, 40, 500, 64), (3, 12, 12, 69, 335, 128), (1, 12, 12, 128, 400, 64),
+              (1, 32, 32, 1, 256, 128), (4, 16, 4, 381, 1375, 64)]
+
+
+@pytest.mark.parametrize("shape", ONE_LAUNCH, ids=lambda s: "x".join(map(str, s)))
+def test_diff_one_launch_is_as_precise_as_the_split(shape):
+    """Where the library runs a differential layer in one launch, its error against float64 is
+    that of the split it would run otherwise: the weights are rounded to bf16 against references
+    taken at the same keys, so the two differ by fp32 rounding (below 1e-5, 1% of an error of
+    1.5e-3) and in the vector producer's finer split of the keys (1 row), which costs the split
+    nothing. A reference kept over all keys gives 1.01 (two partitions) to 1.23 (ten)."""
+    B, Hq, Hkv, Sq, Skv, D = shape
+    T = ef.ef_attention_splitkv_partition_size(*shape, 0)
+    assert T < Skv and ef.ef_diff_attention_workspace_size(*shape, 0) == 0
+    q1, q2, k1, k2, v, lam, gamma = wl.make_diff_inputs(*shape, seed=11)
+    announce(f"diff precision {shape}")
+    dev = [t.cuda() for t in (q1, q2, k1, k2, v) + tuple(lam) + (gamma,)]
+    one, split = (ef.diff_attention(*dev, wl.DIFF_LAMBDA_INIT, wl.DIFF_EPS, causal=True,
+                                    partition_size=p).cpu().double().numpy() for p in (0, T))
+    ref = oracle.diff_attention_ref(f64(q1), f64(q2), f64(k1), f64(k2), f64(v), *map(f64, lam),
+                                    f64(gamma), wl.DIFF_LAMBDA_INIT, wl.DIFF_EPS,
+                                    1.0 / math.sqrt(D), True)
+    e1, e2 = np.linalg.norm(one - ref), np.linalg.norm(split - ref)
+    assert e1 <= 1.005 * e2, f"{shape}: {e1 / e2:.4f} of the split's error"
