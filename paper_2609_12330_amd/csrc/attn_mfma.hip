@@ -24,7 +24,7 @@
 // 64-key tiles. While the vector ALU turns subtile j's scores into weights, the
 // matrix core forms subtile j + 1's scores and multiplies subtile j - 1's
 // values: three subtiles are in flight, so nothing the wave issues during a
-// subtile depends on anything else in it, and the source fixes the order of
+// subtile waits for another kind of its work, and the source fixes the order of
 // issue product by product (see struct Rolling). K is staged one tile ahead of
 // V, two stages each, one workgroup barrier per 64 keys.
 //
@@ -413,7 +413,7 @@ __device__ __forceinline__ void static_for(F&& f) {
 // maximum on every step and spent about a hundred scalar instructions on tile
 // addresses; its matrix cores were busy 54% of the time on 8192 keys at
 // D = 128, whatever order the compiler issued the step in. Here
-//  - all products of a step are independent of the softmax beside them, and
+//  - all products of a subtile are independent of the softmax beside them, and
 //    scheduling barriers pin one product, its share of the vector work (3-4
 //    instructions) and the fragment reads PF products ahead to each slot;
 //  - the maximum is only taken when a lane's sum of weights passes 2^8
@@ -436,9 +436,11 @@ struct Rolling {
   static constexpr int SLOTS = KSTEPS + NV;    // products of a subtile
   static constexpr int PF = 6;                 // slots a fragment is read ahead of its product
 
-  // Products of a subtile in issue order: scores and values alternate, so no
-  // product follows the one it accumulates onto; the last two are values, so
-  // the scores are complete when the next subtile reads them.
+  // Products of a subtile in issue order: scores and values alternate, so that
+  // a product rarely follows the one it accumulates onto. The last two are
+  // values, so the scores are complete when the next subtile reads them; that
+  // leaves the last two scores one behind the other, the subtile's one dependent
+  // pair.
   static constexpr bool is_score(int i) {
     return i < SLOTS - 4 ? i % 2 == 0 : i < SLOTS - 2;
   }
@@ -664,10 +666,11 @@ struct GroupTiles {
 };
 
 // Loads of 64-key tiles into the stages of the rolling loop. Wave w of the NW
-// that share the stages loads the rows [64 w / NW, 64 (w + 1) / NW) of a tile, one 1 KiB block of whole rows per
-// instruction; block i lies i KiB further both in memory and in LDS, so the
-// instruction offset serves both and only the lane offsets of K, whose chunk
-// permutation has a period of 16 rows, differ from block to block.
+// that share the stages loads the rows [64 w / NW, 64 (w + 1) / NW) of a tile, one
+// 1 KiB block of whole rows per instruction; block i lies i KiB further both in
+// memory and in LDS, so the instruction offset serves both and only the lane
+// offsets of K, whose chunk permutation has a period of 16 rows, differ from block
+// to block.
 //
 // The waves that share a V stage are NV, at least the NW that share a K stage: the
 // two groups of a differential launch read the same values.
@@ -817,8 +820,8 @@ enum Form {
 // Occupancy target: two waves per SIMD (two workgroups of four waves per CU, four
 // of the streaming loop's two-wave ones, overlap each other's barrier and
 // latency stalls; a workgroup of eight waves has both on its own), three at D = 64
-// where the registers allow; the four-wave two-group form and the two-wave workgroup of the rolling loop serve
-// grids too small for that.
+// where the registers allow; the four-wave two-group form and the two-wave
+// workgroup of the rolling loop serve grids too small for that.
 template <int D, int NW, Form F>
 __global__ __launch_bounds__(NW * 64 * (F >= kKeySplit ? 2 : 1))
 __attribute__((amdgpu_waves_per_eu(NW == 2 && F != kStream         ? 1
@@ -973,12 +976,11 @@ void attn_mfma_kernel(MfmaParams a) {
         pipelined_step<D, NW, 1>(smem, ld, kh, vh, tl, j + 1, lim, lo, h, kread, vread, qf, sacc,
                                  oacc, lsum, mref, c);
     }
-    if (mref == kNoRef) mref = kNegInf;
   }
 
   // Output rows: value / sum, or the state of the partition, of the value tiles
   // [DT0, DT0 + NDT) (32 channels each; lane halves hold alternate 4-channel runs).
-  auto store = [&](const floatx16* val, int dt0, auto ndt, float ref, float ltot, bool state) {
+  auto store = [&](const floatx16* val, int dt0, auto ndt, float ref, float ltot) {
     constexpr int NDT = decltype(ndt)::value;
     if (!rvalid) return;
     auto put = [&](float* dst, float mul) {
@@ -994,7 +996,7 @@ void attn_mfma_kernel(MfmaParams a) {
       put(a.o + orow * D, ltot > 0.f ? 1.f / ltot : 0.f);
     } else {
       const size_t slot = orow * (size_t)a.P + p;
-      if (state && h == 0) {
+      if (h == 0) {
         // Reference in natural-log units, in terms of scale * q.k.
         a.ws_m[slot] = ref == kNegInf || ref == kNoRef ? kNegInf : ref * kLn2;
         a.ws_l[slot] = ltot;
@@ -1004,7 +1006,7 @@ void attn_mfma_kernel(MfmaParams a) {
   };
 
   if constexpr (STREAM) {
-    store(oacc, 0, std::integral_constant<int, DT>{}, mref, lsum + __shfl_xor(lsum, 32, 64), true);
+    store(oacc, 0, std::integral_constant<int, DT>{}, mref, lsum + __shfl_xor(lsum, 32, 64));
     return;
   } else {
     // The four stages are objects of their own, and the loads go through buffer
@@ -1088,14 +1090,15 @@ void attn_mfma_kernel(MfmaParams a) {
     }
     const float ltot = lsum + __shfl_xor(lsum, 32, 64);  // both lane halves of the row
     if constexpr (GROUPS == 1) {
-      store(oacc, 0, std::integral_constant<int, DT>{}, mref, ltot, true);
+      store(oacc, 0, std::integral_constant<int, DT>{}, mref, ltot);
     } else {
       // The groups meet: each sends the other half of its value tiles (and its
       // reference and sum), and finishes its own half of the channels.
       constexpr int HT = DT / 2;
       const float inv = ltot > 0.f ? 1.f / ltot : 0.f;
       float4* out = reinterpret_cast<float4*>(grp ? sk1 : sk0) + wave * (HT * 4 * 64) + lane;
-      const float4* in = reinterpret_cast<const float4*>(grp ? sk0 : sk1) + wave * (HT * 4 * 64) + lane;
+      const float4* in =
+          reinterpret_cast<const float4*>(grp ? sk0 : sk1) + wave * (HT * 4 * 64) + lane;
       float2* ml = reinterpret_cast<float2*>(sv0);  // [group][wave][lane]
       float* sq2 = reinterpret_cast<float*>(sv1);   // [group][wave][lane]
       floatx16 own[HT];
@@ -1132,7 +1135,7 @@ void attn_mfma_kernel(MfmaParams a) {
             own[i][4 * q4 + 2] = fmaf(x.z, wi, own[i][4 * q4 + 2] * wo);
             own[i][4 * q4 + 3] = fmaf(x.w, wi, own[i][4 * q4 + 3] * wo);
           }
-        store(own, grp * HT, std::integral_constant<int, HT>{}, ref, lt, grp == 0);
+        store(own, grp * HT, std::integral_constant<int, HT>{}, ref, lt);
       } else {
         // y = A1 - lambda A2 (the first group holds the first branch), then the
         // RMS normalisation of the row over all channels.

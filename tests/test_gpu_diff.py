@@ -2,9 +2,10 @@
 sharing v, their learned weighted difference RMS-normalised per head) through
 the C ABI against the fp64 oracle, with the bar of the other parity tests:
 max |o - ref| <= 1e-2 and mean |o - ref| <= 1e-3 over every compared output.
-The single-pass path (one partition) fuses the epilogue into the first
-branch's attention kernel; the split path fuses it into the first branch's
-combine. Every case prints its name before it touches the GPU.
+The single-pass path (one partition) runs both branches and the epilogue in
+one launch, a group of waves per branch; the split path fuses the epilogue
+into the first branch's combine. Every case prints its name before it touches
+the GPU.
 """
 
 import math
