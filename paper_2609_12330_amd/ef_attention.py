@@ -239,7 +239,10 @@ def _stream_handle(stream) -> Optional[int]:
     if stream is not None:
         return stream.cuda_stream
     c = _torch()._C
-    return c._cuda_getCurrentRawStream(c._cuda_getDevice())
+    try:
+        return c._cuda_getCurrentRawStream(c._cuda_getDevice())
+    except AttributeError:  # torch's own names, not its public ones: a release may lack them
+        return _torch().cuda.current_stream().cuda_stream
 
 
 def _check_qkv(q, k, v):

@@ -439,6 +439,32 @@ def test_binding_fails_loudly_without_library(monkeypatch):
         ef.library()
 
 
+def test_stream_handle_without_torchs_private_names(monkeypatch):
+    """The current stream's handle comes from the public call where torch has no raw one."""
+    class Stream:
+        cuda_stream = 0x77
+
+    class Cuda:
+        @staticmethod
+        def current_stream():
+            return Stream
+
+    class Raw:
+        _cuda_getDevice = staticmethod(lambda: 3)
+        _cuda_getCurrentRawStream = staticmethod(lambda device: 0x100 + device)
+
+    class Torch:
+        _C, cuda = Raw, Cuda
+
+    monkeypatch.setattr(ef, "_TORCH", Torch)
+    assert ef._stream_handle(None) == 0x103
+    assert ef._stream_handle(Stream) == 0x77
+    for gone in ("_cuda_getCurrentRawStream", "_cuda_getDevice"):
+        monkeypatch.setattr(Torch, "_C", type("C", (), {
+            k: v for k, v in vars(Raw).items() if k != gone}))
+        assert ef._stream_handle(None) == 0x77
+
+
 def test_product_path_never_imports_the_oracle():
     pkg = os.path.join(ROOT, "paper_2609_12330_amd")
     for dirpath, _, files in os.walk(pkg):
