@@ -259,10 +259,23 @@ double ef_attention_splitkv_modeled_us(int B, int Hq, int Hkv, int Sq, int Skv, 
  * peak; the smallest wins, and with equal times the one with less matrix
  * work. `keys`: the keys a row tile streams (Skv for a full or causal
  * prefill, the partition size in a split-KV call). Returns 0 for invalid
- * sizes or keys < 0. (A single-pass launch too small to fill the chip runs
- * 64-row tiles whose keys two groups of waves share, whatever this returns.)
+ * sizes or keys < 0. The split-KV calls run what this returns; a single-pass
+ * launch too small to fill the chip runs 64-row tiles whose keys two groups of
+ * waves share instead, which ef_attention_fwd_schedule reports.
  */
 int ef_attention_rows_per_workgroup(int B, int Hq, int Hkv, int Sq, int Skv, int D, int keys);
+
+/*
+ * How ef_attention_fwd (window = 0) or ef_attention_fwd_local runs these sizes:
+ * the query rows per workgroup (64 or 128), plus EF_SCHEDULE_KEY_SPLIT when two
+ * groups of waves share a workgroup's key tiles, plus EF_SCHEDULE_LONGEST_FIRST
+ * when row tiles run longest first over the heads of a die instead of head by
+ * head. Returns 0 for invalid sizes and when there is nothing to attend.
+ */
+#define EF_SCHEDULE_KEY_SPLIT 256
+#define EF_SCHEDULE_LONGEST_FIRST 512
+int ef_attention_fwd_schedule(int B, int Hq, int Hkv, int Sq, int Skv, int D, int causal,
+                              int window, int sinks);
 
 /*
  * Measures the best partition size for these inputs on this device: the six

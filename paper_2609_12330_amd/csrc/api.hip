@@ -267,13 +267,13 @@ ef_status from_hip(hipError_t e) { return e == hipSuccess ? EF_OK : EF_ERR_HIP; 
 // 64 KiB at D = 64 (two), so the line is one round of them; causal launches whose
 // workgroups get much shorter towards the end go a quarter past it (with a
 // window, or few queries over a long context, they do not: 8/2 heads of 64, 5 x
-// 865 of 4771 keys with a 792-key window [550] 25.6 / 26.4). Measured, one group of 64 or
-// 128 rows against two groups (us; 64-row tiles in brackets): D = 128 full,
-// 4096^2 x 4 heads [256] 66.9 / 47.6; causal 1024 of 8192
-// keys x 16 heads [256] 127.0 / 87.0, 32/8 heads 640 [320] 17.7 / 16.8, 777 [392]
-// 20.4 / 20.8, 16/4 heads 2048 [512] 39.5 / 41.8; 64 rows of 4000 keys x 32 [32]
-// 63.2 / 45.7; D = 64, 4 x 16 heads 384 full [384] 10.2 / 9.8, 16 heads 2048
-// causal [512] 29.7 / 23.6, 8 x 12 heads 384 full [576] 13.5 / 15.9.
+// 865 of 4771 keys with a 792-key window [550] 25.6 / 26.4). Measured, one group
+// of 64 or 128 rows against two groups (us; 64-row tiles in brackets): D = 128
+// full, 4096^2 x 4 heads [256] 66.9 / 47.6; causal 1024 of 8192 keys x 16 heads
+// [256] 127.0 / 87.0, 32/8 heads 640 [320] 17.7 / 16.8, 777 [392] 20.4 / 20.8,
+// 16/4 heads 2048 [512] 39.5 / 41.8; 64 rows of 4000 keys x 32 [32] 63.2 / 45.7;
+// D = 64, 4 x 16 heads 384 full [384] 10.2 / 9.8, 16 heads 2048 causal [512] 29.7
+// / 23.6, 8 x 12 heads 384 full [576] 13.5 / 15.9.
 bool use_key_split(const Shape& s, const ef::KeyRuns& runs, int causal) {
   const long long R = (long long)(s.Hq / s.Hkv) * s.Sq;
   const long long tiles = (long long)s.B * s.Hkv * ((R + 63) / 64);
@@ -296,6 +296,17 @@ bool longest_first(const Shape& s, const ef::KeyRuns& runs, int causal) {
          (long long)s.B * s.Hkv % ef::kXcds == 0;
 }
 
+// How a single-pass launch runs: query rows per workgroup, key tiles shared by two
+// groups of waves, row tiles longest first.
+struct FwdSchedule {
+  int bm, key_split, interleave;
+};
+
+FwdSchedule fwd_schedule(const Shape& s, const ef::KeyRuns& runs, int causal) {
+  const int split = use_key_split(s, runs, causal) ? 1 : 0;
+  return {split ? 64 : rows_per_block(s, runs.lv), split, longest_first(s, runs, causal) ? 1 : 0};
+}
+
 ef_status launch_mfma(const Shape& s, const void* q, const void* k, const void* v, float* o,
                       float* ws_m, float* ws_l, float* ws_acc, int T, int P, float scale,
                       int causal, const ef::KeyRuns& runs, hipStream_t stream,
@@ -315,7 +326,6 @@ ef_status launch_mfma(const Shape& s, const void* q, const void* k, const void* 
   a.T = T;
   a.P = P;
   a.bm = rows_per_block(s, std::min(T, runs.lv));
-  a.mtiles = (a.R + a.bm - 1) / a.bm;
   a.c_abs = std::fabs(scale) * ef::kLog2e;
   a.qflip = scale < 0.f ? 0x80008000u : 0u;
   a.causal = causal ? 1 : 0;
@@ -326,13 +336,12 @@ ef_status launch_mfma(const Shape& s, const void* q, const void* k, const void* 
     a.diff = *diff;
     a.renew = renew;
   } else if (ws_m == nullptr) {
-    a.interleave = longest_first(s, runs, causal) ? 1 : 0;
-    if (use_key_split(s, runs, causal)) {
-      a.key_split = 1;
-      a.bm = 64;
-      a.mtiles = (a.R + 63) / 64;
-    }
+    const FwdSchedule f = fwd_schedule(s, runs, causal);
+    a.bm = f.bm;
+    a.key_split = f.key_split;
+    a.interleave = f.interleave;
   }
+  a.mtiles = (a.R + a.bm - 1) / a.bm;
   return from_hip(ef::launch_mfma_attention(a, stream));
 }
 
@@ -639,6 +648,17 @@ int ef_attention_rows_per_workgroup(int B, int Hq, int Hkv, int Sq, int Skv, int
   const Shape s{B, Hq, Hkv, Sq, Skv, D};
   if (check_shape(s) != EF_OK || keys < 0) return 0;
   return rows_per_block(s, keys);
+}
+
+int ef_attention_fwd_schedule(int B, int Hq, int Hkv, int Sq, int Skv, int D, int causal,
+                              int window, int sinks) {
+  const Shape s{B, Hq, Hkv, Sq, Skv, D};
+  if (check_shape(s) != EF_OK || window < 0 || sinks < 0) return 0;
+  if (s.rows() == 0 || Skv == 0) return 0;
+  const FwdSchedule f =
+      fwd_schedule(s, key_runs(Sq, Skv, window, sinks), causal != 0 || window > 0 ? 1 : 0);
+  return f.bm + (f.key_split ? EF_SCHEDULE_KEY_SPLIT : 0) +
+         (f.interleave ? EF_SCHEDULE_LONGEST_FIRST : 0);
 }
 
 ef_status ef_attention_splitkv_tune(const void* q, const void* k, const void* v, float* o, int B,

@@ -58,6 +58,7 @@ SIGNATURES = {
     "ef_attention_splitkv_local_workspace_size": (_sz, [_i, _i, _i, _i, _i, _i, _i, _i, _i]),
     "ef_attention_splitkv_modeled_us": (ctypes.c_double, [_i, _i, _i, _i, _i, _i, _i, _i, _i]),
     "ef_attention_rows_per_workgroup": (_i, [_i, _i, _i, _i, _i, _i, _i]),
+    "ef_attention_fwd_schedule": (_i, [_i, _i, _i, _i, _i, _i, _i, _i, _i]),
     "ef_attention_splitkv_tune": (_i, [_vp, _vp, _vp, _fp, _i, _i, _i, _i, _i, _i, _f, _i, _i, _i,
                                        _vp, _sz, _vp, ctypes.POINTER(ctypes.c_int)]),
     "ef_diff_attention": (_i, [_vp, _vp, _vp, _vp, _vp, _fp, _fp, _fp, _fp, _fp, _fp, _f, _f, _i,
@@ -205,6 +206,15 @@ def ef_attention_splitkv_modeled_us(B, Hq, Hkv, Sq, Skv, D, window, sinks, parti
 
 def ef_attention_rows_per_workgroup(B, Hq, Hkv, Sq, Skv, D, keys) -> int:
     return _lib().ef_attention_rows_per_workgroup(B, Hq, Hkv, Sq, Skv, D, keys)
+
+
+# Bits of ef_attention_fwd_schedule's result beside the rows per workgroup.
+SCHEDULE_KEY_SPLIT = 256
+SCHEDULE_LONGEST_FIRST = 512
+
+
+def ef_attention_fwd_schedule(B, Hq, Hkv, Sq, Skv, D, causal, window=0, sinks=0) -> int:
+    return _lib().ef_attention_fwd_schedule(B, Hq, Hkv, Sq, Skv, D, int(causal), window, sinks)
 
 
 def ef_attention_splitkv_tune(q, k, v, o, B, Hq, Hkv, Sq, Skv, D, scale, causal, window, sinks,

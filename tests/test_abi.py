@@ -377,6 +377,50 @@ def test_rows_per_workgroup_choice():
 
 
 @needs_lib
+def test_fwd_schedule():
+    """The form of a single-pass launch on both sides of each line: two groups of waves share
+    the key tiles up to one round of 64-row workgroups (256 at D = 128, 512 at 64; a quarter more
+    where causal tiles get short), row tiles run longest first where causal tiles differ in
+    length and the kv heads divide over the eight dies."""
+    KS, LF = ef.SCHEDULE_KEY_SPLIT, ef.SCHEDULE_LONGEST_FIRST
+    form = ef.ef_attention_fwd_schedule
+    for D, slots in ((128, 256), (64, 512)):
+        # heads x one 64-row tile each, full attention
+        assert form(1, slots, slots, 64, 200, D, 0) == 64 + KS
+        assert form(1, slots + 1, slots + 1, 64, 200, D, 0) == 64
+        assert form(1, slots, slots, 64, 64, D, 0) == 64  # one key tile: nothing to share
+        assert form(1, slots, slots, 64, 65, D, 0) == 64 + KS
+        # the rows of a grouped head fill tiles together: 4 * 65 rows are five tiles of 64
+        kv = slots // 5
+        assert form(1, 4 * kv, kv, 65, 2000, D, 0) == 64 + KS
+        assert form(1, 4 * (kv + 1), kv + 1, 65, 2000, D, 0) == 128
+        # a causal launch with short last tiles: a quarter more, up to twice as many keys as rows
+        tiles = slots + slots // 4
+        odd = 7  # kv heads, not a multiple of eight
+        assert form(odd, 1, 1, 64 * (tiles // odd), 64 * (tiles // odd), D, 1) == 64 + KS
+        assert form(odd, 1, 1, 64 * (tiles // odd + 1), 64 * (tiles // odd + 1), D, 1) == 128
+        n = 64 * (tiles // odd)
+        assert form(odd, 1, 1, n, 2 * n, D, 1) == 64 + KS
+        assert form(odd, 1, 1, n, 2 * n + 1, D, 1) == 128
+        assert form(odd, 1, 1, n, n, D, 0) == 128
+        assert form(odd, 1, 1, n, n, D, 1, window=100) == 128
+        # longest first: causal, no window, up to four times as many keys as rows, 8 | B * Hkv
+        assert form(2, 32, 8, 1000, 1000, D, 1) == 128 + LF
+        assert form(2, 32, 8, 1000, 4000, D, 1) == 128 + LF
+        assert form(2, 32, 8, 1000, 4001, D, 1) == 128
+        assert form(2, 32, 8, 1000, 1000, D, 0) == 128
+        assert form(2, 32, 8, 1000, 1000, D, 1, window=100) == 128
+        assert form(2, 32, 8, 1000, 1000, D, 1, window=1000) == 128 + LF  # hides nothing
+        assert form(7, 12, 12, 1000, 1000, D, 1) == 128
+        assert form(2, 8, 8, 64, 100, D, 1) == 64 + KS + LF
+    assert form(1, 4, 4, 64, 64, 64, 0) == 64
+    assert form(1, 3, 2, 8, 64, 128, 0) == 0     # Hq not a multiple of Hkv
+    assert form(1, 4, 2, 8, 64, 96, 0) == 0      # unsupported head dimension
+    assert form(1, 4, 2, 8, 64, 128, 0, window=-1) == 0
+    assert form(1, 4, 2, 0, 64, 128, 0) == 0 == form(1, 4, 2, 8, 0, 128, 0)
+
+
+@needs_lib
 def test_roofline_partition_choice():
     """partition_size = 0 takes the candidate the roofline model rates fastest. On MI355X the
     picks below were the measured best of 64, 128, ..., 8192 keys per partition (or within 3%
