@@ -285,15 +285,22 @@ bool use_key_split(const Shape& s, const ef::KeyRuns& runs, int causal) {
 // Whether a single-pass launch visits its row tiles longest first over all heads
 // of an XCD. Head by head, the last head's longest tiles start late and end the
 // launch alone; this pays where causal tiles differ in length (few queries over
-// a long context, or a window, make them nearly equal, and then the heads' K/V
-// only compete for the L2: 32 heads, 4096 of 16384 keys, 4096-key window 272 ->
-// 282 us). Head by head / longest first (us): causal, 32/8 heads of 128, 4 x 2048
-// 161.9 / 158.4, 8 x 1024 109 / 103.6, 4 x 1000 of 3000 172.4 / 168.8; 16 heads,
-// 8 x 1024 70.3 / 61.1; 12 heads of 64, 16 x 1024 59.2 / 51.3; 32/8 heads, 4 x 4096
-// 525.6 / 526.5.
+// a long context, or a window, make them nearly equal: 32 heads, 4096 of 16384
+// keys, 4096-key window 272 -> 282 us) and as long as the K/V of an XCD's heads,
+// which are then all in use at once, stay in the caches (4 MiB of L2 per XCD, 256
+// MiB behind all of them). Head by head / longest first (us; MiB of K/V per XCD
+// in brackets): causal, D = 128, 32/8 heads, 4 x 2048 145.9 / 144.3 [4], 4 x 4096
+// 525.8 / 522.1 [8], 32 heads 2048 56.0 / 48.1 [4], 8192 517 / 497 [16], 4 x 2048
+// 179 / 167 [16]; D = 64, 32 heads, 4 x 1024 38.8 / 31.7 [4], 16384 1118 / 1081
+// [16]. Past that the order loses: D = 64, 16 x 12 heads 4096 483 / 492 [24]; D =
+// 128, 4 x 32 heads 4096 570 / 590 [32], 4096 of 8192 1483 / 1817 [64], of 16384
+// 3348 / 4430 [128], 16 x 12 heads 4096 850 / 989 [48].
+constexpr long long kLongestFirstKvBytes = 16LL << 20;
+
 bool longest_first(const Shape& s, const ef::KeyRuns& runs, int causal) {
-  return causal && runs.window == 0 && s.Skv <= 4LL * s.Sq &&
-         (long long)s.B * s.Hkv % ef::kXcds == 0;
+  const long long kv_heads = (long long)s.B * s.Hkv;
+  return causal && runs.window == 0 && s.Skv <= 4LL * s.Sq && kv_heads % ef::kXcds == 0 &&
+         kv_heads / ef::kXcds * s.Skv * s.D * 4 <= kLongestFirstKvBytes;
 }
 
 // How a single-pass launch runs: query rows per workgroup, key tiles shared by two

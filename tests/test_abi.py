@@ -381,7 +381,7 @@ def test_fwd_schedule():
     """The form of a single-pass launch on both sides of each line: two groups of waves share
     the key tiles up to one round of 64-row workgroups (256 at D = 128, 512 at 64; a quarter more
     where causal tiles get short), row tiles run longest first where causal tiles differ in
-    length and the kv heads divide over the eight dies."""
+    length, the kv heads divide over the eight dies and a die's K/V take at most 16 MiB."""
     KS, LF = ef.SCHEDULE_KEY_SPLIT, ef.SCHEDULE_LONGEST_FIRST
     form = ef.ef_attention_fwd_schedule
     for D, slots in ((128, 256), (64, 512)):
@@ -413,6 +413,11 @@ def test_fwd_schedule():
         assert form(2, 32, 8, 1000, 1000, D, 1, window=1000) == 128 + LF  # hides nothing
         assert form(7, 12, 12, 1000, 1000, D, 1) == 128
         assert form(2, 8, 8, 64, 100, D, 1) == 64 + KS + LF
+        # 16 MiB of K/V per die: 4 heads of 8192 keys at D = 128
+        keys = 8192 * 128 // D
+        assert form(1, 32, 32, keys, keys, D, 1) == 128 + LF
+        assert form(1, 32, 32, keys, keys + 1, D, 1) == 128
+        assert form(4, 32, 32, 4096, 8192, D, 1) == 128  # 64 or 32 MiB
     assert form(1, 4, 4, 64, 64, 64, 0) == 64
     assert form(1, 3, 2, 8, 64, 128, 0) == 0     # Hq not a multiple of Hkv
     assert form(1, 4, 2, 8, 64, 96, 0) == 0      # unsupported head dimension
