@@ -315,13 +315,16 @@ ef_status ef_attention_splitkv_tune(const void* q, const void* k, const void* v,
  *   lambda_q1, lambda_k1, lambda_q2, lambda_k2, norm_weight : [D] fp32 device
  *            buffers, shared by all heads; norm_weight 16-byte aligned.
  *   lambda_init, eps : finite, eps >= 0 (else EF_ERR_INVALID_DIFF).
- *   partition_size : 0 (the library's choice: one partition when the query rows
- *            alone fill the chip, else as for ef_attention_splitkv) or a
- *            positive multiple of 64. When the resolved partition covers every
+ *   partition_size : 0 (the library's choice: one partition when the key axis
+ *            is short or the query rows fill whole rounds of the chip, else as
+ *            for ef_attention_splitkv) or a positive multiple of 64. When the resolved partition covers every
  *            key both branches run in one single-pass launch and the workspace
  *            is not used (it may be NULL); otherwise each branch runs the split-KV
  *            producer into `workspace` (ef_diff_attention_workspace_size bytes,
- *            16-byte aligned, reused by both branches) and its combine.
+ *            16-byte aligned, reused by both branches) and its combine. With
+ *            partition_size 0 and 192 or more tiles of 128 query rows (B * Hkv *
+ *            ceil(Sq * Hq/Hkv / 128), Sq * Hq/Hkv > 64) a missing, small or
+ *            misaligned workspace means one launch too.
  * Other errors as for ef_attention_splitkv; all buffers are caller-owned and
  * the call is asynchronous on `stream`.
  */
@@ -335,8 +338,8 @@ ef_status ef_diff_attention(const void* q1, const void* q2, const void* k1, cons
 
 /*
  * Workspace bytes ef_diff_attention needs for this shape and partition_size:
- * 0 when the resolved partition covers every key (single pass), else the
- * split-KV workspace of one branch. Returns 0 for invalid arguments too.
+ * 0 when the resolved partition covers every key (single pass) with and without
+ * a causal mask, else the split-KV workspace of one branch. Returns 0 for invalid arguments too.
  */
 size_t ef_diff_attention_workspace_size(int B, int Hq, int Hkv, int Sq, int Skv, int D,
                                         int partition_size);

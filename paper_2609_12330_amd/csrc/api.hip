@@ -743,15 +743,58 @@ ef_status ef_attention_splitkv_tune(const void* q, const void* k, const void* v,
 
 namespace {
 
-// Row tiles of 128 rows from which a differential layer left to the library
-// runs as one launch over both branches (a workgroup of eight waves per tile and
-// CU) whatever the model would split: from about three quarters of the chip's
-// CUs on, the second producer, the two combines and the stored states cost more
-// than the idle CUs. Measured, split / one launch (us): 12 heads of 64, 4 x 512
-// of 2048 keys [192 tiles] 63.6 / 43.6; 32/8 heads of 128, 1024 of 8192 [256]
-// 282 / 237; 32 heads, 1024 of 32768 [256] 1003 / 968; but 512 of 16384 [128]
-// 290 / 411.
+// Row tiles of 128 rows from which a differential layer left to the library may
+// run as one launch over both branches (a workgroup of eight waves per tile and
+// CU) where the model would split: from about three quarters of the chip's CUs
+// on, the second producer, the two combines and the stored states can cost more
+// than the idle CUs. Measured below the line, split / one launch (us): 512 of
+// 16384 keys, 128 tiles 290 / 411.
 constexpr long long kDiffPairTiles = 192;
+
+// Times of the two ways from that line on (us). One launch runs ceil(tiles / 256)
+// rounds of one workgroup per CU over the keys a row sees: 30 ns a key with every
+// CU at work (18.3 at D = 64), 23 (16) with few, since the clock rises. The split's
+// two producers share the work evenly but for the idle part of their last round
+// and, under a causal mask with about as many queries as keys, partitions that end
+// early; the partition states go through HBM twice, at 5.5 TB/s. Split / one launch
+// measured (us): 1024 causal queries of 8192, 17472 and 65536 keys, row tiles in
+// brackets, D = 128 [192] 236 / 206, 479 / 453, 1528 / 1672; [256] 273 / 244, 636 /
+// 531, 2020 / 1973; [272] 346 / 417, 701 / 900, 2338 / 3700; [384] 437 / 433, -, 3031
+// / 3718; [640] 734 / 677, 1599 / 1441, 4936 / 5866; D = 64 [192] 157 / 142, 271 / 296,
+// 871 / 1094; [256] 176 / 153, 362 / 321, 1254 / 1226; [272] 205 / 279, 392 / 593, 1356
+// / 2409; 9 heads of 128, 4096 of 4096 keys [288] causal 160 / 128, full 219 / 231.
+// Over 150 such points, 192 to 1024 tiles of 2048 to 65536 keys, the pick was the
+// faster way or within 2.3% of it.
+constexpr double kDiffKeyUs128 = 30.0e-3, kDiffKeyUs64 = 18.3e-3;
+constexpr double kDiffLoneKeyUs128 = 23.0e-3, kDiffLoneKeyUs64 = 16.0e-3;
+constexpr double kDiffRenewCost = 1.015;       // renewals of the reference
+constexpr double kDiffSplitKeyUs64 = 17.0e-3;  // at D = 128 as in one launch
+constexpr double kDiffSplitIdle = 0.5;         // part of the last round's idle share that shows
+constexpr double kDiffSplitCausal = 0.4;
+constexpr double kDiffStateBytesPerUs = 5.5e6;
+constexpr double kDiffSplitUs = 18.0;  // three more launches
+
+bool diff_one_launch_faster(const Shape& s, int T, int causal) {
+  const double R = (double)(s.Hq / s.Hkv) * s.Sq;
+  const double rounds = (double)s.B * s.Hkv * std::ceil(R / 128.0) / 256.0;
+  const double keys = s.Skv, queries = s.Sq, P = std::ceil(keys / T);
+  double mean = keys, early = 0.0;  // keys a row sees; queries per key of a causal mask
+  if (causal) {
+    mean = queries <= keys ? keys - queries / 2 : keys * keys / (2 * queries);
+    early = std::min(1.0, queries / keys);
+  }
+  const double key_us = s.D == 128 ? kDiffKeyUs128 : kDiffKeyUs64;
+  const double lone_us = s.D == 128 ? kDiffLoneKeyUs128 : kDiffLoneKeyUs64;
+  const double whole = std::floor(rounds), rest = rounds - whole;
+  const double last = rest > 0 ? lone_us + (key_us - lone_us) * rest * rest * rest : 0.0;
+  const double one = std::max((whole * key_us + last) * mean, lone_us * keys) * kDiffRenewCost;
+  const double split_key_us = s.D == 128 ? kDiffKeyUs128 : kDiffSplitKeyUs64;
+  const double idle = kDiffSplitIdle * (std::ceil(rounds * P) / (rounds * P) - 1.0);
+  const double work = 1.0 + idle + kDiffSplitCausal * early * early;
+  const double split = rounds * split_key_us * mean * work +
+                       4.0 * s.rows() * P * (s.D + 2) * 4.0 / kDiffStateBytesPerUs + kDiffSplitUs;
+  return one <= split;
+}
 
 // And on short key axes, where two producers and two combines cost more than one
 // workgroup's chain of tiles, whatever the grid. Measured, split / one launch
@@ -763,19 +806,25 @@ int diff_pair_keys(int D, long long R) {
   return R <= kDecodeMaxRows ? 256 : D == 64 ? 896 : 640;
 }
 
+// Whether the library may run this layer in one launch without being asked for
+// one partition.
+bool diff_pair_grid(const Shape& s) {
+  const long long R = (long long)(s.Hq / s.Hkv) * s.Sq;
+  return R > 64 && (long long)s.B * s.Hkv * ((R + 127) / 128) >= kDiffPairTiles;
+}
+
 // Number of partitions ef_diff_attention uses (1 = single pass), or 0 for an
 // invalid shape or partition size. *T_out: keys per partition of the caller's or
 // the model's split, also where one launch takes its place.
-long long diff_partitions(const Shape& s, int partition_size, int* T_out) {
+long long diff_partitions(const Shape& s, int partition_size, int causal, int* T_out) {
   if (check_shape(s) != EF_OK) return 0;
   if (partition_size < 0 || partition_size % kTileKeys != 0) return 0;
   if (s.rows() == 0 || s.Skv == 0) return 1;
   const long long R = (long long)(s.Hq / s.Hkv) * s.Sq;
   const int T = resolve_partition(s, s.Skv, partition_size, s.Skv);
   *T_out = T;
-  if (partition_size == 0 &&
-      (s.Skv <= diff_pair_keys(s.D, R) ||
-       (R > 64 && (long long)s.B * s.Hkv * ((R + 127) / 128) >= kDiffPairTiles)))
+  if (partition_size == 0 && (s.Skv <= diff_pair_keys(s.D, R) ||
+                              (diff_pair_grid(s) && diff_one_launch_faster(s, T, causal))))
     return 1;
   return (s.Skv + (long long)T - 1) / T;
 }
@@ -833,8 +882,14 @@ ef_status ef_diff_attention(const void* q1, const void* q2, const void* k1, cons
   // No keys: A1 = A2 = 0, so y = 0 and every output row is 0.
   if (s.Skv == 0) return from_hip(ef::launch_zero_fill(o, (size_t)s.rows() * s.D, hs));
   int T = 0;
-  const long long P = diff_partitions(s, partition_size, &T);
+  long long P = diff_partitions(s, partition_size, causal, &T);
   if (P > kMaxGridYZ) return EF_ERR_INVALID_PARTITION;
+  // Large grids left to the library do without a workspace: they run in one launch,
+  // if slower.
+  const WsLayout w = ws_layout(s.rows(), P, s.D);
+  if (partition_size == 0 && diff_pair_grid(s) &&
+      (workspace == nullptr || workspace_bytes < w.bytes || misaligned(workspace)))
+    P = 1;
   const ef::DiffParams diff{lambda_q1, lambda_k1, lambda_q2, lambda_k2, norm_weight, lambda_init,
                             eps};
   const ef::KeyRuns runs = key_runs(Sq, Skv, 0, 0);
@@ -848,7 +903,6 @@ ef_status ef_diff_attention(const void* q1, const void* q2, const void* k1, cons
     return launch_mfma(s, q1, k1, v, o, nullptr, nullptr, nullptr, runs.lv, 1, scale, causal,
                        runs, hs, q2, k2, &diff, renew);
   }
-  const WsLayout w = ws_layout(s.rows(), P, s.D);
   if (workspace == nullptr || workspace_bytes < w.bytes) return EF_ERR_WORKSPACE_TOO_SMALL;
   if (misaligned(workspace)) return EF_ERR_MISALIGNED;
   char* ws = static_cast<char*>(workspace);
@@ -861,7 +915,8 @@ size_t ef_diff_attention_workspace_size(int B, int Hq, int Hkv, int Sq, int Skv,
                                         int partition_size) {
   const Shape s{B, Hq, Hkv, Sq, Skv, D};
   int T = 0;
-  const long long P = diff_partitions(s, partition_size, &T);
+  const long long P = std::max(diff_partitions(s, partition_size, 0, &T),
+                               diff_partitions(s, partition_size, 1, &T));
   if (P <= 1 || P > kMaxGridYZ) return 0;
   return ws_layout(s.rows(), P, s.D).bytes;
 }

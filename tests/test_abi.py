@@ -467,6 +467,31 @@ def test_roofline_partition_choice():
 
 
 @needs_lib
+def test_diff_one_launch_choice():
+    """A differential layer left to the library runs in one launch where its row tiles fill
+    whole rounds of the chip's 256 CUs, and in split branches where a last round would be
+    nearly empty over a long key axis. Each pick was the faster of the two measured, or within
+    3% of it; the times stand at the rule."""
+    def one(heads, kv_heads, Sq, Skv, D, B=1):
+        return ef.ef_diff_attention_workspace_size(B, heads, kv_heads, Sq, Skv, D, 0) == 0
+
+    for D in (64, 128):
+        for tiles, keys, want in [(256, 5184, True), (256, 8192, True), (224, 17472, True),
+                                  (192, 8192, True), (192, 65536, False), (264, 32768, False),
+                                  (272, 5184, False), (272, 17472, False), (272, 65536, False),
+                                  (304, 8192, False), (384, 32768, False), (640, 5184, True),
+                                  (640, 65536, False), (128, 17472, False)]:
+            assert one(tiles // 8, tiles // 8, 1024, keys, D) == want, (tiles, keys, D)
+        assert not one(32, 8, 1088, 17472, D)   # 272 tiles of grouped heads
+        assert not one(32, 8, 1200, 66736, D)
+        assert one(32, 8, 1088, 400, D)         # short key axis
+    # an explicit partition size is the caller's
+    ws = ef.ef_diff_attention_workspace_size
+    assert ws(1, 34, 34, 1024, 17472, 128, 17472 + 64 - 17472 % 64) == 0
+    assert ws(1, 32, 32, 1024, 8192, 128, 4096) > 0
+
+
+@needs_lib
 def test_tune_validation():
     import ctypes as C
     t = C.c_int(0)

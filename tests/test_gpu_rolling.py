@@ -304,3 +304,42 @@ def test_diff_one_launch_is_as_precise_as_the_split(shape):
                                     1.0 / math.sqrt(D), True)
     e1, e2 = np.linalg.norm(one - ref), np.linalg.norm(split - ref)
     assert e1 <= 1.005 * e2, f"{shape}: {e1 / e2:.4f} of the split's error"
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_diff_past_one_round(D):
+    """More row tiles than CUs (272): the library splits the keys, bit for bit as the caller's
+    own partition of that size does, and without a workspace runs one launch. The two ways differ
+    by the rounding of each weight to bf16 in another place: bound as in
+    test_diff_pair_key_counts, once for each."""
+    B, H, Hkv, Sq, n = 1, 34, 34, 1024, 5184
+    shape = (B, H, Hkv, Sq, n, D)
+    q1, q2, k1, k2, v, lam, gamma = wl.make_diff_inputs(*shape, seed=13)
+    announce(f"diff past one round {shape}")
+    dev = [t.cuda() for t in (q1, q2, k1, k2, v)]
+    vecs = [t.cuda() for t in tuple(lam) + (gamma,)]
+    T = ef.splitkv_partition_size(*shape)
+    assert T < n and ef.ef_diff_attention_workspace_size(*shape, 0) > 0
+    args = (wl.DIFF_LAMBDA_INIT, wl.DIFF_EPS)
+    chosen = ef.diff_attention(*dev, *vecs, *args, causal=True)
+    assert torch.equal(chosen, ef.diff_attention(*dev, *vecs, *args, causal=True,
+                                                 partition_size=T))
+    o = torch.full_like(chosen, math.nan)
+    ptrs = [t.data_ptr() for t in dev + [o] + vecs]
+    assert ef.ef_diff_attention(*ptrs, *args, *shape, 1.0 / math.sqrt(D), True, 0, None, 0,
+                                torch.cuda.current_stream().cuda_stream) == 0
+    h = slice(33, 34)
+    a1, a2 = (oracle.attention_ref(f64(q[:, h]), f64(k[:, h]), f64(v[:, h]), 1.0 / math.sqrt(D),
+                                   True) for q, k in ((q1, k1), (q2, k2)))
+    l64 = [t.double().numpy() for t in lam]
+    mix = np.exp(l64[0] @ l64[1]) - np.exp(l64[2] @ l64[3]) + wl.DIFF_LAMBDA_INIT
+    y = a1 - mix * a2
+    rms = np.sqrt((y * y).mean(-1, keepdims=True) + wl.DIFF_EPS)
+    g = gamma.double().numpy() * (1.0 - wl.DIFF_LAMBDA_INIT)
+    dy = 2.0 ** -9 * float(v.float().abs().max()) * (1.0 + abs(mix))
+    bound = np.abs(g) * (dy / rms) * (1.0 + np.abs(y) / rms) + 1e-6
+    for got in (chosen, o):
+        err = np.abs(got[:, h].cpu().double().numpy() - g * y / rms)
+        assert (err <= bound).all(), f"{(err / bound).max():.3f} of bound"
+    both = np.broadcast_to(bound.max(), chosen.shape)  # of every head: the same distributions
+    assert (np.abs((chosen - o).cpu().double().numpy()) <= 2 * both).all()
