@@ -79,8 +79,8 @@ ef::KeyRuns key_runs(int Sq, int Skv, int window, int sinks) {
 // the modelled resources). Resources: HBM (K/V, q, o and the partial states
 // written and read back) and the streaming time of one workgroup (T keys of K
 // and V, or the fewer keys its rows can see, at that workgroup's rate, times
-// the rounds of workgroups the chip holds); the combine follows (inside the producer for up to 64 partitions,
-// else a second kernel). The rates were fitted to partition-size sweeps of
+// the rounds of workgroups the chip holds); the combine follows (inside the
+// producer for up to 64 partitions, else a second kernel). The rates were fitted to partition-size sweeps of
 // twelve decode shapes on MI355X (1 to 64 query rows per kv head, 1K to 128K
 // keys): the VALU producer streams 6.5 TB/s over the chip and 27.6, 51.1 or
 // 10.3 GB/s per workgroup for 1, 2 or 4 query rows per kv head (one, two and
@@ -92,6 +92,15 @@ ef::KeyRuns key_runs(int Sq, int Skv, int window, int sinks) {
 // load a wave draws about 16 GB/s (VALU) or 8.5 GB/s (MFMA), counted over the
 // waves weighted by their share of the keys (a short last partition adds
 // little).
+// The rates of 3 or 4 rows are those of one wave per partition, while up to 512
+// partitions now run four (launch_decode_split) and take 10-40% less than modelled:
+// over 142 decode shapes (1 to 16 sequences, 2 to 8 kv heads, 512 to 65536 keys) the
+// pick is 5.4% slower than the best size in the mean, 28% at most (2 x 32/8 heads,
+// 8192 keys: 64 keys 20.8 us, 512 keys 17.4). A model of both forms came within 1.6%
+// on those shapes, but on 70 others the sizes it chose instead (mostly 2 to 8 times
+// larger) were 1.3% faster in the mean and up to 25% slower, and fewer references
+// mean more rounding: the error against 64 bits grew by 15% in the mean, 3.6 times
+// where 64 keys had held 16 per wave. So the choice stays with the one-wave rates.
 constexpr double kHbmValuBytesPerUs = 6.5e6;
 constexpr double kHbmMfmaBytesPerUs = 5.85e6;
 constexpr double kWgValuBytesPerUs[3] = {27.6e3, 51.1e3, 10.3e3};  // 1, 2, 4 rows
