@@ -246,7 +246,7 @@ ef_status ef_attention_combine(const float* m, const float* l, const float* acc,
  * one partition holding every key) this model rates fastest.
  * Returns a negative value for invalid arguments. (With 3 or 4 query rows per
  * kv head and at most 512 partitions over all heads the producer runs four waves
- * per partition; the model rates one, 10-40% slower.)
+ * per partition; the model rates one, which is 1.1 to 3 times slower.)
  */
 double ef_attention_splitkv_modeled_us(int B, int Hq, int Hkv, int Sq, int Skv, int D,
                                        int window, int sinks, int partition_size);

@@ -93,7 +93,7 @@ ef::KeyRuns key_runs(int Sq, int Skv, int window, int sinks) {
 // waves weighted by their share of the keys (a short last partition adds
 // little).
 // The rates of 3 or 4 rows are those of one wave per partition, while up to 512
-// partitions now run four (launch_decode_split) and take 10-40% less than modelled:
+// partitions now run four (launch_decode_split) and take 9-70% less than modelled:
 // over 142 decode shapes (1 to 16 sequences, 2 to 8 kv heads, 512 to 65536 keys) the
 // pick is 5.4% slower than the best size in the mean, 28% at most (2 x 32/8 heads,
 // 8192 keys: 64 keys 20.8 us, 512 keys 17.4). A model of both forms came within 1.6%
