@@ -805,7 +805,10 @@ enum Form {
 // between two launches, and each V tile is staged once for both. 32/8 heads of
 // 128, 1024 causal: 52.5 -> 37.0 us, 4 x 1024: 118.5 -> 105.8 us; 32 heads, 1024 of
 // 32768 keys: 1003 us in two split branches, 999 in one launch, 968 with the
-// shared V stages.
+// shared V stages. Grids of thousands of row tiles of grouped heads of 64 lose up
+// to 3% against a launch per branch, whose four-wave workgroups run three waves to
+// a SIMD: 15 x 32/8 heads, 1321 of 2227 keys 715 us before, 734 now, 11 x 64/8, 762
+// of 886 245 and 252 (ungrouped heads gain there too: 4 x 32, 1024 87 and 82).
 //
 // kDiffRenew is kDiffPair where the launch takes the place of a split call: every
 // a.renew key tiles, the tiles of one of the split's partitions, a row's reference

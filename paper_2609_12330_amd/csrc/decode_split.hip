@@ -468,12 +468,17 @@ constexpr int kSlots = RMAX <= 2 ? 4 : 2;
 // With 3 or 4 rows per kv head and few workgroups (two per CU or fewer), four
 // waves share each partition: one wave per partition leaves most SIMDs empty,
 // has too few loads in flight and, as the last arrival, combines the group's
-// rows with 64 threads. The line is where four waves stop winning on every
-// shape tried, one wave / four waves (us), 32/8 heads of 128: 2 x 8192 keys in
-// 256s [512 workgroups] 22.8 / 19.9, 4 x 4096 in 256s [512] 24.0 / 18.9, 1 x
-// 4096 [256] 15.1 / 11.1, 16/4 heads 65536 in 1024s [256] 66.5 / 30.4; heads of
+// rows with 64 threads. The line is where four waves stop winning with partitions
+// of 256 keys and more, one wave / four waves (us), 32/8 heads of 128: 2 x 8192
+// keys in 256s [512 workgroups] 22.8 / 19.9, 4 x 4096 in 256s [512] 24.0 / 18.9, 1
+// x 4096 [256] 15.1 / 11.1, 16/4 heads 65536 in 1024s [256] 66.5 / 30.4; heads of
 // 64, 2 x 8192 in 256s [512] 15.3 / 14.7; but 4 x 6144 in 256s [768] 24.6 / 30.7
-// and 8 x 4096 [1024] 27.9 / 33.6. (1 or 2 rows: within 10% either way.) It
+// and 8 x 4096 [1024] 27.9 / 33.6. (1 or 2 rows: within 10% either way.) On
+// partitions too short to fill four waves (64 keys, 128 at D = 64) more than 256
+// workgroups are 3-14% slower so: 32/8 heads of 64, 4096 keys in 64s [512] 11.7 /
+// 13.3, 16 x 512 in 128s [512] 10.7 / 11.6. They keep the form for its error
+// against 64 bits: every wave has a reference of its own, and the same two calls
+// are at 4.6e-4 and 1.20e-3 with four waves, 1.45e-3 and 1.54e-3 with one. The line
 // counts partitions only, so every channel split of a problem has the same
 // waves and the same sums.
 constexpr long long kWideWorkgroups = 512;
