@@ -185,9 +185,9 @@ double split_model_us(const Shape& s, int keys, int T, int visible) {
   return std::max(r_hbm, r_wg) + combine;
 }
 
-// Candidate partition sizes for a key axis of `keys` keys: 64, 128, 192, 256,
-// 384, 512, ... (powers of two times 64 and 1.5 times them), up to one
-// partition holding every key; at most 65535 partitions.
+// Candidate partition sizes for a key axis of `keys` keys: 64, 128, 256, 512,
+// ... (powers of two times 64), up to one partition holding every key; at most
+// 65535 partitions.
 std::vector<int> partition_candidates(int keys) {
   std::vector<int> out;
   const long long top = ((long long)std::max(keys, 1) + kTileKeys - 1) / kTileKeys * kTileKeys;

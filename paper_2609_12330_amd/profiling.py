@@ -208,8 +208,8 @@ def main():
     a = ap.parse_args()
 
     stats = kernel_stats(a.stats)
-    lines = [f"# {a.kernel} on {a.workload}", "", "Commands (from the repository root on the GPU "
-             "box, `cd /tmp && export TMPDIR=/tmp` first):", "", "```", a.command, "```", "",
+    lines = [f"# {a.kernel} on {a.workload}", "", "Commands (from the repository root, "
+             "`cd /tmp && export TMPDIR=/tmp` first):", "", "```", a.command, "```", "",
              "## rocprofv3 --kernel-trace --stats", "",
              "| kernel | calls | avg us | min us | max us | % time |", "|---|---|---|---|---|---|"]
     for s in stats:
