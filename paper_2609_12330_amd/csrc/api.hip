@@ -760,6 +760,9 @@ namespace {
 // 16384 keys, 128 tiles 290 / 411.
 constexpr long long kDiffPairTiles = 192;
 
+// Largest partition whose references one launch in its place renews.
+constexpr int kRenewKeys = 8192;
+
 // Times of the two ways from that line on (us). One launch runs ceil(tiles / 256)
 // rounds of one workgroup per CU over the keys a row sees: 30 ns a key with every
 // CU at work (18.3 at D = 64), 23 (16) with few, since the clock rises. The split's
@@ -796,7 +799,8 @@ bool diff_one_launch_faster(const Shape& s, int T, int causal) {
   const double lone_us = s.D == 128 ? kDiffLoneKeyUs128 : kDiffLoneKeyUs64;
   const double whole = std::floor(rounds), rest = rounds - whole;
   const double last = rest > 0 ? lone_us + (key_us - lone_us) * rest * rest * rest : 0.0;
-  const double one = std::max((whole * key_us + last) * mean, lone_us * keys) * kDiffRenewCost;
+  const double one = std::max((whole * key_us + last) * mean, lone_us * keys) *
+                     (T <= kRenewKeys ? kDiffRenewCost : 1.0);
   const double split_key_us = s.D == 128 ? kDiffKeyUs128 : kDiffSplitKeyUs64;
   const double idle = kDiffSplitIdle * (std::ceil(rounds * P) / (rounds * P) - 1.0);
   const double work = 1.0 + idle + kDiffSplitCausal * early * early;
@@ -907,8 +911,11 @@ ef_status ef_diff_attention(const void* q1, const void* q2, const void* k1, cons
     // often as the split's partitions would have set one of their own: each sets
     // its largest weight to exactly 1, free of the rounding to bf16. Without the
     // renewal the error against 64 bits was 23% above the split's with ten 64-key
-    // partitions (640 keys: 2.06e-3, split 1.66e-3), 0.5% with five of 2048.
-    const int renew = T < Skv ? T / kTileKeys : 0;
+    // partitions (640 keys: 2.06e-3, split 1.66e-3), 0.5% with five of 2048, 0.2%
+    // with two of 4096. With partitions of 16384 keys the two agree (-0.2% to 0.1%
+    // over eight pairs of inputs), and the plain form is 1.2% faster (32 heads of
+    // 128, 1024 of 32768 keys 1020 / 1008 us).
+    const int renew = T < Skv && T <= kRenewKeys ? T / kTileKeys : 0;
     return launch_mfma(s, q1, k1, v, o, nullptr, nullptr, nullptr, runs.lv, 1, scale, causal,
                        runs, hs, q2, k2, &diff, renew);
   }
